@@ -55,9 +55,12 @@ WsLayout ws_layout(int64_t h, int64_t w) {
 
 static bool finite_pos(float v) { return std::isfinite(v) && v > 0.0f; }
 
-int64_t fused_max_px() {
-  if (const char* env = std::getenv("LACOSMIC_FUSED_MAX_PX")) return std::atoll(env);
-  return kFusedMaxPx;
+int fused_form(int64_t h, int64_t w, const lacosmic_params& p, bool caller_ws) {
+  if (p.flags & LACOSMIC_F_FULL_SP) return kFusedOff;
+  const char* env = std::getenv("LACOSMIC_FUSED_MAX_PX");
+  const int64_t limit = env ? std::atoll(env) : caller_ws ? kFusedMaxPx : kMaxPixels;
+  if (h * w > limit) return kFusedOff;
+  return caller_ws ? kFusedPingPong : kFusedTiles;
 }
 
 int check_params(int64_t h, int64_t w, const lacosmic_params* p) {
@@ -418,7 +421,7 @@ int lacosmic_run_ex(const float* img, int64_t h, int64_t w, const lacosmic_param
       ws = static_cast<char*>(c->ws);
     }
     FrameDev f = make_frame(img, h, w, *p, out_mask, out_clean, ws, L, c->cfg);
-    f.fused = use_fused(h, w, *p) ? 1 : 0;
+    f.fused = fused_form(h, w, *p, workspace != nullptr);
     FrameDev* fd = reinterpret_cast<FrameDev*>(ws + L.rec);
     if (launch_put_frame(f, fd, s) != hipSuccess) return LACOSMIC_EHIP;
     if (c->use_graphs) {  // the recorded run for this workspace and shape

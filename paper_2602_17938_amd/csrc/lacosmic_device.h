@@ -52,6 +52,12 @@ struct GainWork {
   double mean, var;                 // of the current round's kept values
 };
 
+// Forms of a run (FrameDev::fused).
+constexpr int kFusedOff = 0;       // the sparse passes
+constexpr int kFusedPingPong = 1;  // one launch per iteration that leaves S, S' and B1 in the
+                                   // workspace (lacosmic_small.h)
+constexpr int kFusedTiles = 2;     // one launch per iteration, results only (lacosmic_iter.h)
+
 // One frame's device state for one run.  The single-frame path passes it by
 // value; the batched and serving paths keep an array of them in device
 // memory.  Bit planes hold one bit per pixel: bit i of word j of row y is
@@ -101,7 +107,7 @@ struct FrameDev {
   int full_sp;                 // compute and keep S' at every pixel
   int est_gain;                // no gain supplied: estimated at each iteration, and every
                                // iteration runs the dense passes (S changes everywhere)
-  int fused;                   // single frame: one fused launch per iteration (small frames)
+  int fused;                   // kFused*: whether an iteration is one launch
   int sepmed;                  // detection medians separable (row medians, then column medians)
   int tiles_x;                 // tiles per row for the launch's tile shape
   int tiles;                   // tiles per frame

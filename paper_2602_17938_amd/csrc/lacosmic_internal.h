@@ -54,15 +54,15 @@ FrameDev make_frame(const float* img, int64_t h, int64_t w, const lacosmic_param
 
 struct BatchCache;
 
-// Frames of at most this many pixels run one fused launch per iteration on
-// the single-frame path (LACOSMIC_FUSED_MAX_PX overrides; 0 turns it off);
-// frames with the full-S' flag never do.
-constexpr int64_t kFusedMaxPx = int64_t(1) << 19;  // measured crossover between 512^2 and 1024^2
-int64_t fused_max_px();
-// Whether a single-frame run of this frame takes the fused launches.
-inline bool use_fused(int64_t h, int64_t w, const lacosmic_params& p) {
-  return !(p.flags & LACOSMIC_F_FULL_SP) && h * w <= fused_max_px();
-}
+// Single-frame runs of at most this many pixels are one launch per iteration
+// (LACOSMIC_FUSED_MAX_PX overrides; 0 turns it off), those with the full-S'
+// flag never.  A run whose workspace the caller cannot look into leaves no S
+// or candidate plane behind and takes the launches of lacosmic_iter.h at any
+// size; one in a caller's workspace leaves them there, which one launch per
+// iteration does faster than the sparse passes only for small frames
+// (crossover measured between 512^2 and 1024^2).
+constexpr int64_t kFusedMaxPx = int64_t(1) << 19;
+int fused_form(int64_t h, int64_t w, const lacosmic_params& p, bool caller_ws);
 
 // A recorded single-frame run (counter reset and every iteration's launches)
 // for one workspace address, frame shape, tile shape, iteration count and

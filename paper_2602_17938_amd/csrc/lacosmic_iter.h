@@ -1,0 +1,1092 @@
+// One whole iteration of a frame in one launch, for runs whose workspace no
+// caller can look into (the library's cached one, the static scratch, a
+// batch, the server): only the mask and the cleaned image are results there,
+// so S, S' and the candidate planes need not exist, and nothing is computed
+// where a bound already decides.
+//
+// One block per tile of TH x TW output pixels.  One iteration reads the
+// previous image and mask within 8 pixels of an output pixel (replacement 2,
+// growths 1 + 1, objlim test 4), so a block works alone from the tile plus an
+// 8-pixel halo (the region) in LDS:
+//
+//   1. C_k over the region (clamped coordinates): the input, with the value
+//      of every pixel of the mask M_k patched in.  The input is never
+//      written, and the values of mask pixels lie in two planes used in
+//      turn, so every block of a launch reads only what earlier launches
+//      wrote.  (The cleaned image is written, never read: all of it in
+//      iteration 0, then the pixels that changed.)
+//   2. Candidates S > sigclip within 4 pixels of the tile.  A bound drops
+//      nearly every pixel first: with v the smallest value of the region,
+//      N >= N(v) (the noise model grows with the median, and a median of the
+//      region's values is at least v), and L <= 2c - min(u, d) - min(l, r)
+//      up to rounding, so a pixel where that is at most 2 sigclip N(v), less
+//      a margin for the rounding, has S <= sigclip.  It costs 5 operations
+//      per pixel where S costs 126.  The rest (about 1 % of the pixels of
+//      the workloads, twice the number of true candidates) get S exactly.
+//   3. S at the pixels within 3 of a candidate, by aligned 2x2 blocks
+//      sharing one median network, kept in an LDS pool (S' at the pixels
+//      within 1 of a candidate reads no other).
+//   4. S' = S - med5(S) at the candidates and, next to one, at the pixels
+//      with S > sigfrac*sigclip: G1, G2.  (The growth reads G2 only within 1
+//      of a pixel of B2, and B2 is a subset of the candidates.)  Where G1
+//      holds, the objlim test: B1.
+//   5. Both growths, M_(k+1), the pixels whose replacement can change (mask
+//      pixels within 2 of a new one) and their values, on bit rows.
+//
+// A tile whose region no value or mask bit changed in during the previous
+// iteration would repeat that iteration's result: it is skipped.  Each tile
+// records which of its 3x3 zones (8 pixels along the edges, and the middle)
+// held a change, and in which of the two mask and value planes its state
+// lies; like the planes, the records alternate between two arrays.
+//
+// Every value that decides anything is computed by the expressions of the
+// sparse path, so the results are the same bit for bit.
+//
+// What bounds it: vector issue and the latency of its phases together (about
+// half the issue slots of a 4096^2 frame's iteration 0, 7.3 k VALU
+// instructions per 64 x 64 tile; a block's dozen phases are separated by
+// barriers, and the sparse ones keep one to three of its four waves busy), so
+// the LDS is cut to 40 KB and the registers to 128 for four blocks per CU
+// (three blocks: 179 -> 140 us for that iteration), and each phase lists its
+// work and runs it on full waves.  Against the chain of about seven launches
+// per iteration of the sparse passes (single frames, four iterations): 512^2
+// 0.179 -> 0.132 ms with the call, 800^2 with eight times the cosmic rays
+// 0.417 -> 0.172, 4096^2 0.479 -> 0.365, 4000 x 6500 0.635 -> 0.468,
+// 6400 x 9600 0.731 -> 0.659.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "lacosmic_device.h"
+#include "lacosmic_tiles.h"
+
+namespace lac {
+
+constexpr int kIterHalo = 8;     // the iteration's dependency radius
+constexpr int kIterThreads = 256;
+constexpr int kIterWaves = 4;    // waves per SIMD the launch bounds ask for (blocks per CU, with its LDS)
+
+// Tile state word of one iteration: bit 0, the plane (of two) that holds the
+// tile's mask bits and values; bit 1 + 3 * zy + zx, zone (zy, zx) of the tile
+// held a changed value or mask bit.
+
+__device__ __forceinline__ uint32_t* iter_state(const FrameDev& f, int it) {
+  return reinterpret_cast<uint32_t*>((it & 1) ? f.rs : f.dirty);
+}
+__device__ __forceinline__ float* iter_values(const FrameDev& f, uint32_t plane) {
+  return reinterpret_cast<float*>(plane ? f.conf : f.list);
+}
+
+// Bit rows of the region: 32 columns per word, each row between two zero
+// words.  One thread per word: a word's neighbours in its row give the bits
+// that a horizontal dilation shifts in.
+struct BitSpan {  // words ww - 1, ww, ww + 1 of a row (or of several ORed)
+  uint32_t l, c, r;
+};
+__device__ __forceinline__ BitSpan operator|(BitSpan x, BitSpan y) {
+  return BitSpan{x.l | y.l, x.c | y.c, x.r | y.r};
+}
+// The middle word of the span dilated by R columns.
+template <int R>
+__device__ __forceinline__ uint32_t span_dil(BitSpan s) {
+  uint32_t o = s.c;
+#pragma unroll
+  for (int k = 1; k <= R; ++k)
+    o |= __builtin_amdgcn_alignbit(s.c, s.l, 32 - k) | __builtin_amdgcn_alignbit(s.r, s.c, k);
+  return o;
+}
+// Columns [lo, hi) as bits of word ww.
+__device__ __forceinline__ uint32_t col_bits(int ww, int lo, int hi) {
+  const int a = clampi(lo - 32 * ww, 32), b = clampi(hi - 32 * ww, 32);
+  const uint32_t below_b = b >= 32 ? ~0u : (1u << b) - 1u, below_a = a >= 32 ? ~0u : (1u << a) - 1u;
+  return below_b & ~below_a;
+}
+
+// Minimum and largest magnitude over a wave, in lane 63 (DPP row shifts and
+// broadcasts).
+__device__ __forceinline__ float vmin(float a, float b) {
+  float d;
+  asm("v_min_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));  // no NaN quieting of its inputs
+  return d;
+}
+__device__ __forceinline__ float vmax(float a, float b) {
+  float d;
+  asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ float vmin3(float a, float b, float c) {
+  float d;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ float vmax3_abs(float a, float b, float c) {  // of |a|, |b|, |c|
+  float d;
+  asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_move(float v) {
+  const int b = __float_as_int(v);
+  return __int_as_float(__builtin_amdgcn_update_dpp(b, b, CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void dpp_step(float& mn, float& mx) {
+  mn = vmin(mn, dpp_move<CTRL, ROWS>(mn));
+  const float o = dpp_move<CTRL, ROWS>(mx);
+  mx = vmax3_abs(mx, o, o);
+}
+__device__ __forceinline__ void wave_min_max(float& mn, float& mx) {
+  dpp_step<0x111, 0xf>(mn, mx);  // row_shr:1, 2, 4, 8
+  dpp_step<0x112, 0xf>(mn, mx);
+  dpp_step<0x114, 0xf>(mn, mx);
+  dpp_step<0x118, 0xf>(mn, mx);
+  dpp_step<0x142, 0xa>(mn, mx);  // row_bcast:15, 31
+  dpp_step<0x143, 0xc>(mn, mx);
+}
+// Keys of n staged values: where the region holds no negative value (a
+// block-uniform choice) a value's bits are its key already.
+template <int N>
+__device__ __forceinline__ void keys_of(int* v, bool nonneg) {
+  if (!nonneg) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] ^= (v[k] >> 31) & 0x7fffffff;
+  }
+}
+
+// Unsigned order-preserving keys (bisection over the floats).
+__device__ __forceinline__ uint32_t gkey_of(float v) { return (uint32_t)fkey(v) ^ 0x80000000u; }
+__device__ __forceinline__ float gkey_float(uint32_t k) { return funkey((int)(k ^ 0x80000000u)); }
+
+// The thread's index, opaque to the optimiser: what a phase derives from it is
+// computed there and not kept in registers across the phases (and the tiles)
+// before, whose networks need them all.
+__device__ __forceinline__ int phase_tid() {
+  int t = (int)threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Bit planes of the region.
+constexpr int kBitM = 0;   // M_k, then M_(k+1)
+constexpr int kBitCd = 1;  // live candidates; then the new mask pixels
+constexpr int kBitD1 = 2;  // pixels within 1 of a live candidate
+constexpr int kBitG1 = 3, kBitG2 = 4, kBitB1 = 5;
+constexpr int kBitDead = 6;  // candidates whose objlim test fails whatever their S'
+constexpr int kBitPlanes = 7;
+
+template <int TH, int TW_>
+struct alignas(16) SmemIter {
+  static constexpr int RH = TH + 2 * kIterHalo, RW = TW_ + 2 * kIterHalo;
+  static constexpr int QR = (RH - 4) / 2, QC = (RW - 4) / 2;  // 2x2 blocks of the S area
+  static constexpr int NW = (RW + 31) / 32;                   // words of a bit row
+  // Rows of the bit planes: region rows 3 .. RH - 4 (nothing reads others),
+  // NW words and a zero word each, and a zero word before the first row.
+  static constexpr int BR0 = 3, BROWS = RH - 2 * BR0;
+  static constexpr int kPlaneWords = (BROWS * (NW + 1) + 1 + 3) / 4 * 4;
+  // 2x2 blocks of S and list items held at once: what the four blocks per CU
+  // leave of its LDS (a denser tile works through bands of rows), or, on
+  // small tiles, every block there is
+  static constexpr int kQuadCap = TW_ == 64 ? 256 : QR * QC, kItemCap = TW_ == 64 ? 512 : 1024;
+  typedef typename std::conditional<(kQuadCap <= 256), uint8_t, uint16_t>::type QIndex;
+  float c[RH][RW];        // C_k at the clamped region coordinates
+  float s4[kQuadCap][4];  // S of the listed 2x2 blocks (before that, [0]: the block's position)
+  uint32_t bits[kBitPlanes][kPlaneWords];
+  uint64_t qbits[QR];      // the 2x2 blocks of the S area to evaluate, a bit row per block row
+  uint16_t lst[kItemCap];  // items: region cell index
+  QIndex qmap[QR * QC];    // a block's index in s4, by position
+  float wmin[kIterThreads / 64], wmax[kIterThreads / 64];
+  float mn, nmin, thr;  // the region's smallest value, the noise there, the candidates' bound
+  unsigned int cnt, nq, n2, fresh, unrep, zones;
+  int any_b1, live;
+  __device__ __forceinline__ static int at(int r, int ww) { return (r - BR0) * (NW + 1) + 1 + ww; }
+  __device__ __forceinline__ BitSpan span(int plane, int r, int ww) const {
+    const uint32_t* p = bits[plane] + at(r, ww) - 1;
+    return BitSpan{p[0], p[1], p[2]};
+  }
+  __device__ __forceinline__ uint32_t& word(int plane, int r, int ww) { return bits[plane][at(r, ww)]; }
+  __device__ __forceinline__ uint32_t word(int plane, int r, int ww) const { return bits[plane][at(r, ww)]; }
+  __device__ __forceinline__ bool bit(int plane, int r, int q) const {
+    return ((word(plane, r, q >> 5) >> (q & 31)) & 1u) != 0u;
+  }
+  __device__ __forceinline__ void set(int plane, int r, int q) {
+    atomicOr(&word(plane, r, q >> 5), 1u << (q & 31));
+  }
+  // The blocks within 3 pixels of live candidate (r, q), and the pixels
+  // within 1 of it.
+  __device__ __forceinline__ void mark_near(int r, int q) {
+    const int c0 = (q - 3) >> 1;  // of 4 block columns, counted from region column 0
+    const uint64_t m = ((0xfull << c0) >> 1) & ((1ull << QC) - 1ull);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int br = ((r - 3) >> 1) - 1 + k;
+      if (br >= 0 && br < QR) atomicOr((unsigned long long*)&qbits[br], (unsigned long long)m);
+    }
+    const int c1 = q - 1, sh = c1 & 31;
+#pragma unroll
+    for (int k = -1; k <= 1; ++k) {
+      uint32_t* p = &word(kBitD1, r + k, c1 >> 5);
+      atomicOr(p, 7u << sh);
+      if (sh > 29) atomicOr(p + 1, 7u >> (32 - sh));
+    }
+  }
+};
+
+// S at the four pixels of the 2x2 block whose top-left region cell is (y, x)
+// (even, at least 2 inside the region); cells outside the frame get values
+// nothing reads.
+template <typename SM>
+__device__ __forceinline__ void iter_quad(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
+                                          int x, bool nonneg, float* S) {
+  int v[36];
+#pragma unroll
+  for (int a = 0; a < 6; ++a)
+#pragma unroll
+    for (int b = 0; b < 6; ++b) v[a * 6 + b] = __float_as_int(s.c[y - 2 + a][x - 2 + b]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int k = ((q >> 1) + 2) * 6 + (q & 1) + 2;
+    S[q] = lap_edge(__int_as_float(v[k]), __int_as_float(v[k - 6]), __int_as_float(v[k + 6]),
+                    __int_as_float(v[k - 1]), __int_as_float(v[k + 1]));
+  }
+  keys_of<36>(v, nonneg);
+  int m[4];
+  med25_block(v, m, f.sepmed);
+  if (noise_fast(nc)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[q] = S[q] / (2.0f * noise_from_med<true>(m[q], nc, f.rn2));
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[q] = S[q] / (2.0f * noise_from_med<false>(m[q], nc, f.rn2));
+  }
+}
+
+// S (and N) at one region cell (2 or more inside the region).
+template <typename SM>
+__device__ __forceinline__ float iter_s(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
+                                        int x, bool nonneg, float& N) {
+  int v[25];
+#pragma unroll
+  for (int a = 0; a < 5; ++a)
+#pragma unroll
+    for (int b = 0; b < 5; ++b) v[a * 5 + b] = __float_as_int(s.c[y - 2 + a][x - 2 + b]);
+  const float L = lap_edge(__int_as_float(v[12]), __int_as_float(v[7]), __int_as_float(v[17]),
+                           __int_as_float(v[11]), __int_as_float(v[13]));
+  keys_of<25>(v, nonneg);
+  const int m = med25_of(v, f.sepmed);
+  N = noise_fast(nc) ? noise_from_med<true>(m, nc, f.rn2) : noise_from_med<false>(m, nc, f.rn2);
+  return L / (2.0f * N);
+}
+
+// On tiles at the frame's edge a window clamps on the frame: its rows and
+// columns outside take the values of the nearest one inside.  For the K x K
+// window v around frame pixel (gy, gx).
+template <int K>
+__device__ __forceinline__ void clamp_window(int* v, const FrameDev& f, int gy, int gx) {
+  constexpr int R = K / 2;
+#pragma unroll
+  for (int a = R - 1; a >= 0; --a) {  // from the centre outwards
+    const bool up = gy - R + a < 0, dn = gy + R - a >= f.h;
+    const bool lf = gx - R + a < 0, rt = gx + R - a >= f.w;
+#pragma unroll
+    for (int b = 0; b < K; ++b) {
+      v[a * K + b] = up ? v[(a + 1) * K + b] : v[a * K + b];
+      v[(K - 1 - a) * K + b] = dn ? v[(K - 2 - a) * K + b] : v[(K - 1 - a) * K + b];
+    }
+#pragma unroll
+    for (int b = 0; b < K; ++b) {
+      v[b * K + a] = lf ? v[b * K + a + 1] : v[b * K + a];
+      v[b * K + K - 1 - a] = rt ? v[b * K + K - 2 - a] : v[b * K + K - 1 - a];
+    }
+  }
+}
+
+// S' at region cell (y, x): S's 5x5 window lies in 3x3 blocks of the pool.
+template <typename SM>
+__device__ __forceinline__ float iter_sprime(const SM& s, const FrameDev& f, int y, int x, int ry0,
+                                             int rx0, bool inner) {
+  int v[25];
+  {
+    const int q0 = (((y - 2) >> 1) - 1) * SM::QC + ((x - 2) >> 1) - 1;
+    float w[36];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const float4 q = *reinterpret_cast<const float4*>(s.s4[s.qmap[q0 + a * SM::QC + b]]);
+        w[(2 * a) * 6 + 2 * b] = q.x;
+        w[(2 * a) * 6 + 2 * b + 1] = q.y;
+        w[(2 * a + 1) * 6 + 2 * b] = q.z;
+        w[(2 * a + 1) * 6 + 2 * b + 1] = q.w;
+      }
+    const bool oy = (y & 1) != 0, ox = (x & 1) != 0;  // the window starts at an odd cell
+#pragma unroll
+    for (int k = 0; k < 30; ++k) w[k] = oy ? w[k + 6] : w[k];
+#pragma unroll
+    for (int a = 0; a < 5; ++a)
+#pragma unroll
+      for (int b = 0; b < 5; ++b)
+        v[a * 5 + b] = __float_as_int(ox ? w[a * 6 + b + 1] : w[a * 6 + b]);
+  }
+  if (!inner) clamp_window<5>(v, f, ry0 + y, rx0 + x);
+  const float S = __int_as_float(v[12]);
+  return S - funkey(med25_of(v, f.sepmed));  // S >= +0: its bits are its key
+}
+
+// The objlim test's parts at region cell (y, x): med3 there, and the test's
+// outcome for a given med7 and S'.  The outcome can only go from failing to
+// holding as med7 grows or as S' grows (rounding keeps the order), so bounds
+// on either decide it.
+template <typename SM>
+__device__ __forceinline__ float iter_med3(const SM& s, const FrameDev& f, int y, int x, bool nonneg) {
+  int v9[9];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) v9[a * 3 + b] = __float_as_int(s.c[y - 1 + a][x - 1 + b]);
+  keys_of<9>(v9, nonneg);
+  return funkey(med9_of(v9, f.sepmed));
+}
+__device__ __forceinline__ bool objlim_holds(const FrameDev& f, float m3, float m7, float N, float spv) {
+  const float fr = (m3 - m7) / N;
+  const float fn = (fr > 0.01f) ? fr : 0.01f;
+  return (spv / fn) > f.objlim;
+}
+// Whether med7 of med3 at (y, x) is at most t, without forming any median: a
+// median is at most t when more than half its values are, so the 9x9 patch
+// becomes rows of bits [C <= t], the 3x3 majorities come from bit-sliced
+// sums of the three rows, and their number in the 7x7 window decides.  About
+// 390 operations, where the medians themselves take 1100.
+template <typename SM>
+__device__ __forceinline__ bool iter_med7_le(const SM& s, const FrameDev& f, int y, int x, int ry0,
+                                             int rx0, bool inner, float t) {
+  uint32_t one[9], two[9];  // per row and column: the sum of 3 neighbours' bits
+#pragma unroll
+  for (int a = 0; a < 9; ++a) {
+    uint32_t r = 0u;
+#pragma unroll
+    for (int b = 8; b >= 0; --b) r = r + r + (s.c[y - 4 + a][x - 4 + b] <= t ? 1u : 0u);
+    const uint32_t r1 = r >> 1, r2 = r >> 2;
+    one[a] = r ^ r1 ^ r2;
+    two[a] = (r & r1) | (r & r2) | (r1 & r2);
+  }
+  uint32_t le[7];  // [med3 <= t] of the 7x7 positions, bit b: column b
+#pragma unroll
+  for (int a = 0; a < 7; ++a) {
+    const uint32_t p0 = two[a], p1 = two[a + 1], p2 = two[a + 2];
+    const uint32_t mj = (p0 & p1) | (p0 & p2) | (p1 & p2);
+    if (f.sepmed) {  // the median of the three row medians
+      le[a] = mj;
+      continue;
+    }
+    // 5 or more of 9: ones s1 + twos (p0 + p1 + p2 + c1) * 2
+    const uint32_t o0 = one[a], o1 = one[a + 1], o2 = one[a + 2];
+    const uint32_t s1 = o0 ^ o1 ^ o2, c1 = (o0 & o1) | (o0 & o2) | (o1 & o2);
+    const uint32_t px = p0 ^ p1 ^ p2, par = px ^ c1, car = px & c1;
+    le[a] = (mj & car) | ((mj ^ car) & (par | s1));
+  }
+  if (!inner) {  // positions outside the frame take the nearest one inside
+    const int gy = ry0 + y, gx = rx0 + x;
+#pragma unroll
+    for (int a = 2; a >= 0; --a) {
+      le[a] = gy - 3 + a < 0 ? le[a + 1] : le[a];
+      le[6 - a] = gy + 3 - a >= f.h ? le[5 - a] : le[6 - a];
+    }
+    const int lf = max(0, 3 - gx), rt = 6 - max(0, gx + 3 - (f.w - 1));  // first and last column inside
+    const uint32_t lm = (1u << lf) - 1u, rm = 0x7fu & ~((2u << rt) - 1u);
+#pragma unroll
+    for (int a = 0; a < 7; ++a)
+      le[a] = (le[a] & ~(lm | rm)) | (((le[a] >> lf) & 1u) ? lm : 0u) | (((le[a] >> rt) & 1u) ? rm : 0u);
+  }
+  int n = 0;
+#pragma unroll
+  for (int a = 0; a < 7; ++a) {
+    const int k = __popc(le[a] & 0x7fu);
+    n += f.sepmed ? (k >= 4 ? 1 : 0) : k;
+  }
+  return n >= (f.sepmed ? 4 : 25);
+}
+
+// The objlim test at region cell (y, x).
+template <typename SM>
+__device__ __forceinline__ bool iter_objlim(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
+                                            int x, int ry0, int rx0, bool inner, bool nonneg, float spv) {
+  const float m3 = iter_med3(s, f, y, x, nonneg);
+  if (objlim_holds(f, m3, s.mn, s.nmin, spv)) return true;  // for the smallest med7 and N there can be
+  float N;
+  (void)iter_s(s, f, nc, y, x, nonneg, N);
+  // The largest med7 for which the test still fails (its value without
+  // rounding is m3 - d): then [med7 <= that] is the answer.
+  const float d = N * (spv / f.objlim), t = m3 - d, e = (fabsf(m3) + d) * 0x1p-21f;
+  if (!objlim_holds(f, m3, t - e, N, spv) && objlim_holds(f, m3, t + e, N, spv)) {
+    uint32_t fails = gkey_of(t - e), holds = gkey_of(t + e);
+#pragma unroll 1
+    while (holds - fails > 1u) {
+      const uint32_t mid = fails + ((holds - fails) >> 1);
+      if (objlim_holds(f, m3, gkey_float(mid), N, spv))
+        holds = mid;
+      else
+        fails = mid;
+    }
+    return !iter_med7_le(s, f, y, x, ry0, rx0, inner, gkey_float(fails));
+  }
+  // (an overflow above: bisect for med7 itself)
+  uint32_t lo = gkey_of(s.mn), hi = 0xff7fffffu;  // keys of the smallest value and the largest float
+#pragma unroll 1
+  while (lo < hi) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    if (iter_med7_le(s, f, y, x, ry0, rx0, inner, gkey_float(mid)))
+      hi = mid;
+    else
+      lo = mid + 1u;
+  }
+  return objlim_holds(f, m3, gkey_float(lo), N, spv);
+}
+
+// The tiles of a frame.
+template <int TH, int TW_>
+struct IterGrid {
+  int tiles_x, tiles_y;
+  __device__ __forceinline__ explicit IterGrid(const FrameDev& f)
+      : tiles_x((f.w + TW_ - 1) / TW_), tiles_y((f.h + TH - 1) / TH) {}
+  // State after the previous iteration of neighbour k (0 .. 8, row-major) of
+  // tile (ty, tx); 0 outside the frame.
+  __device__ __forceinline__ uint32_t state(const uint32_t* prev, int ty, int tx, int k) const {
+    const int qy = ty + k / 3 - 1, qx = tx + k % 3 - 1;
+    const bool in = qy >= 0 && qy < tiles_y && qx >= 0 && qx < tiles_x;
+    const uint32_t v = ldg(prev, in ? qy * tiles_x + qx : ty * tiles_x + tx);
+    return in ? v : 0u;
+  }
+};
+
+// Of tiles t0 .. t0 + n - 1 (n <= 64), those iteration it >= 1 has work for:
+// a value or mask bit changed within their region in the previous iteration.
+// The others' state carries over.  Every wave of the block gets the same set.
+template <int TH, int TW_>
+__device__ __forceinline__ unsigned long long iter_active(const FrameDev& f, int it, int t0, int n) {
+  const int lane = threadIdx.x & 63;
+  const IterGrid<TH, TW_> g(f);
+  bool act = false;
+  if (lane < n) {
+    const uint32_t* prev = iter_state(f, it - 1);
+    const int t = t0 + lane, ty = t / g.tiles_x, tx = t - ty * g.tiles_x;
+    uint32_t st[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) st[k] = g.state(prev, ty, tx, k);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      // zones of that tile the region overlaps: all of them (the tile
+      // itself), else its edge towards this tile
+      const uint32_t zr = k < 3 ? 0x1c0u : k < 6 ? 0x1ffu : 0x007u;
+      const uint32_t zc = k % 3 == 0 ? 0x124u : k % 3 == 1 ? 0x1ffu : 0x049u;
+      act |= ((st[k] >> 1) & zr & zc) != 0u;
+    }
+    if (!act && threadIdx.x < 64) stg(iter_state(f, it), t, st[4] & 1u);
+  }
+  return __ballot(act);
+}
+
+// The iteration on one tile, by kIterThreads threads; every barrier is
+// block-uniform.
+template <int TH, int TW_>
+__device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, SmemIter<TH, TW_>& s) {
+  using SM = SmemIter<TH, TW_>;
+  constexpr int NT = kIterThreads, RH = SM::RH, RW = SM::RW, QR = SM::QR, QC = SM::QC, NW = SM::NW;
+  constexpr int HL = kIterHalo, QCAP = SM::kQuadCap, ICAP = SM::kItemCap;
+  static_assert(TW_ == 32 || TW_ == 64, "a tile row is a half or a whole bit-plane word");
+  static_assert(SM::BROWS * NW <= NT && TH % 2 == 0, "one thread per word of the bit rows");
+  int tid = phase_tid();
+  const int lane = tid & 63;
+  const int h = f.h, w = f.w;
+  const IterGrid<TH, TW_> grid(f);
+  const int ty = tile / grid.tiles_x, tx = tile - ty * grid.tiles_x;
+  const int y0 = ty * TH, x0 = tx * TW_;
+  const int ry0 = y0 - HL, rx0 = x0 - HL;
+  uint32_t st[9];  // planes of the 3x3 tiles after the previous iteration
+  if (it > 0) {
+    const uint32_t v = grid.state(iter_state(f, it - 1), ty, tx, lane < 9 ? lane : 4);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) st[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k) & 1u;
+  }
+  const uint32_t plane = it > 0 ? st[4] : 1u;  // this iteration writes plane ^ 1
+  const bool inner = ry0 >= 0 && rx0 >= 0 && ry0 + RH <= h && rx0 + RW <= w;
+  const int fc0 = rx0 < 0 ? -rx0 : 0, fc1 = min(RW, w - rx0);  // region columns inside the frame
+  auto row_in = [&](int r) __attribute__((always_inline)) { return ry0 + r >= 0 && ry0 + r < h; };
+  int wr = tid / NW + SM::BR0, ww = tid % NW;  // this thread's word of the bit rows
+  bool wt = tid < SM::BROWS * NW;
+  auto next_phase = [&]() __attribute__((always_inline)) {
+    tid = phase_tid();
+    wr = tid / NW + SM::BR0;
+    ww = tid % NW;
+    wt = tid < SM::BROWS * NW;
+  };
+
+  // ---- 1. stage C_k and M_k
+  if (tid == 0) {
+    s.cnt = 0u;
+    s.fresh = 0u;
+    s.unrep = 0u;
+    s.zones = 0u;
+    s.any_b1 = 0;
+    s.live = 0;
+  }
+  const float* src = f.img;
+  const uint16_t* src16 = f.img16;
+  float mn = __int_as_float(0x7f800000), mx = 0.0f;
+  uint32_t mword = 0u;  // M_k: word mq of region row mr
+  const int mr = tid / NW, mq = tid - mr * NW;
+  static_assert(RH * NW <= NT, "one thread per word of M_k");
+  if (it > 0 && mr < RH && row_in(mr)) {
+    // the tile's own columns and 8 of each neighbour
+    const int64_t gy = ry0 + mr;
+    const uint32_t sl = mr < HL ? st[0] : mr < HL + TH ? st[3] : st[6];
+    const uint32_t sc = mr < HL ? st[1] : mr < HL + TH ? st[4] : st[7];
+    const uint32_t sr = mr < HL ? st[2] : mr < HL + TH ? st[5] : st[8];
+    auto word = [&](uint32_t p, int t) __attribute__((always_inline)) -> uint64_t {
+      if (t < 0 || t >= grid.tiles_x) return 0ull;
+      const uint64_t* m = p ? f.mbits[1] : f.mbits[0];
+      if (TW_ == 64) return ldg(m, gy * f.wpr + t);
+      return ldg(reinterpret_cast<const uint32_t*>(m), gy * f.wpr * 2 + t);
+    };
+    const uint64_t cw = word(sc, tx);
+    if (mq == 0) mword = (uint32_t)((word(sl, tx - 1) >> (TW_ - 8)) & 0xffull) | ((uint32_t)cw << 8);
+    if (mq == NW - 1) mword = (uint32_t)(cw >> (TW_ - 8)) | ((uint32_t)(word(sr, tx + 1) & 0xffull) << 8);
+    if (NW == 3 && mq == 1) mword = (uint32_t)(cw >> 24);
+  }
+  if (inner) {
+    // C4 threads per row of 16-byte groups, RP rows at a time
+    constexpr int C4 = RW / 4, RP = NT / C4, K = (RH + RP - 1) / RP;
+    typedef uint16_t h4u __attribute__((ext_vector_type(4), aligned(2)));
+    const int r0 = tid / C4, q0 = 4 * (tid - r0 * C4);
+    const uint32_t o0 = (uint32_t)(r0 * w + q0), step = (uint32_t)(RP * w);  // from the region's corner
+    const int64_t corner = (int64_t)ry0 * w + rx0;
+    auto put = [&](int k, float a, float b, float c, float d) __attribute__((always_inline)) {
+      const int r = r0 + k * RP;
+      if (RP * C4 != NT && r0 >= RP) return;
+      if (K * RP != RH && r >= RH) return;
+      a += 0.0f;  // -0 becomes +0
+      b += 0.0f;
+      c += 0.0f;
+      d += 0.0f;
+      mn = vmin3(vmin3(mn, a, b), c, d);
+      mx = vmax3_abs(vmax3_abs(mx, a, b), c, d);
+      *reinterpret_cast<float4*>(&s.c[r][q0]) = float4{a, b, c, d};
+    };
+    // (threads and rows past the region load its last row again)
+    auto at = [&](int k) __attribute__((always_inline)) -> uint32_t {
+      return (r0 + k * RP < RH) ? o0 + (uint32_t)k * step : o0;
+    };
+    if (src16) {
+      const uint16_t* base = src16 + corner;
+      h4u v[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) h4u*)(base + at(k));
+#pragma unroll
+      for (int k = 0; k < K; ++k) put(k, (float)v[k].x, (float)v[k].y, (float)v[k].z, (float)v[k].w);
+    } else {
+      const float* base = src + corner;
+      f4u v[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) f4u*)(base + at(k));
+#pragma unroll
+      for (int k = 0; k < K; ++k) put(k, v[k].x, v[k].y, v[k].z, v[k].w);
+    }
+  } else {
+#pragma unroll 4
+    for (int i = tid; i < RH * RW; i += NT) {
+      const int r = i / RW, q = i - r * RW;
+      const int64_t gi = (int64_t)clampi(ry0 + r, h - 1) * w + clampi(rx0 + q, w - 1);
+      const float v = (src16 ? (float)ldg(src16, gi) : ldg(src, gi)) + 0.0f;
+      mn = vmin(mn, v);
+      mx = vmax3_abs(mx, v, v);
+      s.c[r][q] = v;
+    }
+  }
+  if (!inner)  // edge tiles read blocks no one lists (and drop what they hold)
+    for (int i = tid; i < QR * QC; i += NT) s.qmap[i] = 0;
+  // the other planes start empty, the words beside each row stay zero
+  for (int i = tid; i < kBitPlanes * SM::kPlaneWords / 4; i += NT)
+    reinterpret_cast<uint4*>(&s.bits[0][0])[i] = uint4{0u, 0u, 0u, 0u};
+  if (tid < QR) s.qbits[tid] = 0ull;
+  __syncthreads();
+  if (it > 0) {
+    // the values of M_k's pixels replace the input's
+    auto value_of = [&](int r, int q) __attribute__((always_inline)) -> float {  // a cell in the frame
+      const int k = (r < HL ? 0 : r < HL + TH ? 3 : 6) + (q < HL ? 0 : q < HL + TW_ ? 1 : 2);
+      uint32_t p = 0;
+#pragma unroll
+      for (int j = 0; j < 9; ++j) p = (j == k) ? st[j] : p;
+      return ldg((const float*)iter_values(f, p), (int64_t)(ry0 + r) * w + rx0 + q);
+    };
+    if (mr >= SM::BR0 && mr < SM::BR0 + SM::BROWS) s.word(kBitM, mr, mq) = mword;
+    const unsigned int nm = __popc(mword);
+    const unsigned int mbase = nm ? atomicAdd(&s.cnt, nm) : 0u;
+    __syncthreads();
+    const unsigned int n = s.cnt;
+    for (unsigned int c0 = 0; c0 < n; c0 += ICAP) {  // listed, then one thread each
+      unsigned int at = mbase - c0;
+      for (uint32_t bits = mword; bits; bits &= bits - 1, ++at)
+        if (at < (unsigned int)ICAP) s.lst[at] = (uint16_t)(mr * RW + 32 * mq + __ffs((int)bits) - 1);
+      __syncthreads();
+      for (unsigned int j = tid; j < min(n - c0, (unsigned int)ICAP); j += NT) {
+        const int i = s.lst[j], r = i / RW, q = i - r * RW;
+        const float v = value_of(r, q);
+        mn = vmin(mn, v);
+        s.c[r][q] = v;
+      }
+      __syncthreads();
+    }
+    if (!inner && n) {  // a cell outside the frame holds the value of its clamped pixel
+      for (int i = tid; i < RH * RW; i += NT) {
+        const int r = i / RW, q = i - r * RW;
+        const int cr = clampi(ry0 + r, h - 1) - ry0, cq = clampi(rx0 + q, w - 1) - rx0;
+        if (cr != r || cq != q) s.c[r][q] = s.c[cr][cq];
+      }
+    }
+  }
+  wave_min_max(mn, mx);
+  next_phase();
+  if ((tid & 63) == 63) {
+    s.wmin[tid >> 6] = mn;
+    s.wmax[tid >> 6] = mx;
+  }
+  const NoiseCoef nc = noise_coef(f, it);
+  const float sigclip = f.sigclip, lo = f.lo;
+  __syncthreads();
+  // ---- 2. candidates.  A pixel can have S > sigclip only where
+  // 2c - min(u, d) - min(l, r) > thr.  The margin: L and the bound are sums
+  // of a few values of magnitude at most 16 M (M the region's largest), each
+  // rounded once, which moves them by less than 2^-18 M together; the
+  // products of the noise model and of S round by less than 2^-20 each.
+  // Where the bound's own arithmetic could over- or underflow, or a value is
+  // not finite, every pixel is tested exactly (thr = -inf).
+  if (tid < 64) {  // one wave for the block
+    if (tid == 0) s.cnt = 0u;
+    mn = vmin(vmin3(s.wmin[0], s.wmin[1], s.wmin[2]), s.wmin[3]);
+    const float M = vmax3_abs(vmax3_abs(s.wmax[0], s.wmax[1], s.wmax[2]), s.wmax[3], s.wmax[3]);
+    const float nmin = noise_from_med<false>(fkey(mn), nc, f.rn2);  // no noise in the region is smaller
+    const bool sane = nc.fast_sqrt && nc.gain >= 0x1p-30f && nc.gain <= 0x1p30f && sigclip >= 0x1p-30f &&
+                      sigclip <= 0x1p30f && M <= 0x1p90f && mn <= M;
+    const float t = (2.0f * sigclip) * nmin * (1.0f - 0x1p-14f) - M * 0x1p-16f;
+    if (tid == 0) {
+      s.mn = mn;
+      s.nmin = nmin;
+      s.thr = (sane && t > 0.0f) ? t : __int_as_float(0xff800000);
+      if (!(M <= 0x1.fffffep127f)) atom_or(f.status, 1);
+    }
+  }
+  constexpr int CG = (TW_ + 8) / 4;             // groups of 4 columns
+  constexpr int SR = TH == 64 ? 8 : 2;          // rows per item
+  constexpr int ITEMS = CG * ((TH + 8) / SR);
+  static_assert(ITEMS <= NT && (TH + 8) % SR == 0 && SR <= 8, "one item per thread");
+  uint32_t hits = 0;
+  const int sg = tid / CG, cg = tid - sg * CG;
+  const int px0 = 4 + 4 * cg, py0 = 4 + SR * sg;
+  __syncthreads();
+  const float thr = s.thr;
+  const bool nonneg = s.mn >= 0.0f;
+  if (tid < ITEMS) {
+    float4 up = *reinterpret_cast<const float4*>(&s.c[py0 - 1][px0]);
+    float4 cu = *reinterpret_cast<const float4*>(&s.c[py0][px0]);
+#pragma unroll
+    for (int k = 0; k < SR; ++k) {
+      const float4 dn = *reinterpret_cast<const float4*>(&s.c[py0 + k + 1][px0]);
+      const float l = s.c[py0 + k][px0 - 1], r = s.c[py0 + k][px0 + 4];
+      const float e0 = __builtin_fmaf(2.0f, cu.x, -(vmin(up.x, dn.x) + vmin(l, cu.y)));
+      const float e1 = __builtin_fmaf(2.0f, cu.y, -(vmin(up.y, dn.y) + vmin(cu.x, cu.z)));
+      const float e2 = __builtin_fmaf(2.0f, cu.z, -(vmin(up.z, dn.z) + vmin(cu.y, cu.w)));
+      const float e3 = __builtin_fmaf(2.0f, cu.w, -(vmin(up.w, dn.w) + vmin(cu.z, r)));
+      hits |= (!(e0 <= thr) ? 1u : 0u) << (4 * k);
+      hits |= (!(e1 <= thr) ? 2u : 0u) << (4 * k);
+      hits |= (!(e2 <= thr) ? 4u : 0u) << (4 * k);
+      hits |= (!(e3 <= thr) ? 8u : 0u) << (4 * k);
+      up = cu;
+      cu = dn;
+    }
+    if (!inner && hits) {  // pixels of the frame only
+#pragma unroll
+      for (int k = 0; k < SR; ++k)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int q = px0 + b;
+          if (!row_in(py0 + k) || q < fc0 || q >= fc1) hits &= ~(1u << (4 * k + b));
+        }
+    }
+  }
+  const unsigned int nhit = __popc(hits);
+  const unsigned int hbase = nhit ? atomicAdd(&s.cnt, nhit) : 0u;
+  __syncthreads();
+  const unsigned int npc = s.cnt;
+  for (unsigned int c0 = 0; c0 < npc; c0 += ICAP) {  // one round unless the tile is dense
+    uint32_t hb = hits;
+    unsigned int at = hbase;
+    while (hb) {
+      const int b = __ffs((int)hb) - 1;
+      hb &= hb - 1;
+      if (at - c0 < (unsigned int)ICAP) s.lst[at - c0] = (uint16_t)((py0 + (b >> 2)) * RW + px0 + (b & 3));
+      ++at;
+    }
+    __syncthreads();
+    const unsigned int n = min(npc - c0, (unsigned int)ICAP);
+    for (unsigned int j = tid; j < n; j += NT) {
+      const int i = s.lst[j], r = i / RW, q = i - r * RW;
+      // a NaN passes every bound, so it arrives here (and every pixel with an
+      // infinite one in the region)
+      if (!finite_bits(s.c[r][q])) atom_or(f.status, 1);
+      float N;
+      const float S = iter_s(s, f, nc, r, q, nonneg, N);
+      if (S > sigclip) {
+        // dead: the objlim test fails even for S' = S.  Not where it holds
+        // for the smallest med7 there can be (cosmic rays); else where med7
+        // lies below the value at which it would hold (stars).
+        const float m3 = iter_med3(s, f, r, q, nonneg);
+        bool dead = false;
+        if (!objlim_holds(f, m3, s.mn, s.nmin, S)) {
+          const float d = N * (S / f.objlim), t = m3 - d - (fabsf(m3) + d) * 0x1p-18f;
+          dead = !objlim_holds(f, m3, t, N, S) && iter_med7_le(s, f, r, q, ry0, rx0, inner, t);
+        }
+        s.set(dead ? kBitDead : kBitCd, r, q);
+        if (!dead) {
+          s.live = 1;
+          s.mark_near(r, q);
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- 3-4. S near the live candidates of rows [b0, b1), S', G1, G2, B1.
+  // False (and no bit set) if their blocks exceed the pool, or the pixels to
+  // evaluate the list.  marked:
+  // the blocks are marked already (by step 2, for all rows).
+  auto detect = [&](int b0, int b1, bool marked) __attribute__((always_inline)) -> bool {
+    __syncthreads();  // every thread has read the counters of the round before
+    next_phase();
+    if (tid == 0) s.nq = s.n2 = 0u;
+    if (!marked) {
+      if (tid < QR) s.qbits[tid] = 0ull;
+      if (wt) s.word(kBitD1, wr, ww) = 0u;
+      __syncthreads();
+      if (wt && wr >= b0 && wr < b1)
+        for (uint32_t d = s.word(kBitCd, wr, ww); d; d &= d - 1) s.mark_near(wr, 32 * ww + __ffs((int)d) - 1);
+    }
+    __syncthreads();
+    constexpr int QW = (QC + 31) / 32;  // words of a block row
+    if (tid < QR * QW) {
+      const int br = tid / QW, half = tid - br * QW;
+      uint64_t row = s.qbits[br];
+      if (!inner) {  // blocks that hold a pixel of the frame
+        const int j0 = max(0, (fc0 - 2) >> 1), j1 = min(QC, (fc1 - 1) >> 1);
+        const bool in = (row_in(2 + 2 * br) || row_in(3 + 2 * br)) && j0 < j1;
+        row &= in ? ((1ull << j1) - 1ull) & ~((1ull << j0) - 1ull) : 0ull;
+      }
+      uint32_t d = (uint32_t)(row >> (32 * half));
+      if (d) {
+        unsigned int at = atomicAdd(&s.nq, (unsigned int)__popc(d));
+        for (; d; d &= d - 1) {
+          const int q = br * QC + 32 * half + __ffs((int)d) - 1;
+          if (at < (unsigned int)QCAP) {
+            s.s4[at][0] = __int_as_float(q);
+            s.qmap[q] = (typename SM::QIndex)at;
+          }
+          ++at;
+        }
+      }
+    }
+    __syncthreads();
+    const unsigned int nq = s.nq;
+    if (nq > (unsigned int)QCAP) return false;
+    for (unsigned int j = tid; j < nq; j += NT) {
+      const int qi = __float_as_int(s.s4[j][0]), br = qi / QC;
+      const int y = 2 + 2 * br, x = 2 + 2 * (qi - br * QC);
+      float S[4];
+      iter_quad(s, f, nc, y, x, nonneg, S);
+      *reinterpret_cast<float4*>(s.s4[j]) = float4{S[0], S[1], S[2], S[3]};
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const int r = y + a;
+        // the live candidates of the rows, and next to one the pixels with
+        // S > lo (G2 off the candidates matters within 2 pixels of the tile)
+        const int rb = clampi(r - SM::BR0, SM::BROWS - 1) + SM::BR0;
+        const uint32_t cw = rb == r ? s.word(kBitCd, rb, x >> 5) >> (x & 31) : 0u;
+        const uint32_t dw = (s.word(kBitD1, rb, x >> 5) >> (x & 31)) & ~cw;
+        const bool rows = r >= b0 && r < b1;
+        const bool g2row = r >= 6 && r < RH - 6 && (inner || row_in(r));
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const bool g2col = x + b >= 6 && x + b < RW - 6 && (inner || (x + b >= fc0 && x + b < fc1));
+          if ((((cw >> b) & 1u) && rows) || (((dw >> b) & 1u) && g2row && g2col && S[2 * a + b] > lo))
+          {
+            const unsigned int at = atomicAdd(&s.n2, 1u);
+            if (at < (unsigned int)ICAP) s.lst[at] = (uint16_t)(r * RW + x + b);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    next_phase();
+    const unsigned int n2 = s.n2;
+    if (n2 > (unsigned int)ICAP) return false;
+    for (unsigned int j = tid; j < n2; j += NT) {
+      const int i = s.lst[j], r = i / RW, q = i - r * RW;
+      const float spv = iter_sprime(s, f, r, q, ry0, rx0, inner);
+      if (spv > lo) s.set(kBitG2, r, q);
+      if (spv > sigclip) {
+        s.set(kBitG1, r, q);
+        if (iter_objlim(s, f, nc, r, q, ry0, rx0, inner, nonneg, spv)) {
+          s.set(kBitB1, r, q);
+          s.any_b1 = 1;
+        }
+      }
+    }
+    __syncthreads();
+    return true;
+  };
+  if (s.live) {  // (uniform: written before a barrier, read after it)
+    constexpr int kBand = 4;  // candidate rows that always fit
+    static_assert((kBand / 2 + 4) * QC <= QCAP && (kBand + 2) * (TW_ + 8) <= ICAP, "a band fits");
+    int rows = RH - 8;  // all at once unless that is too much
+    // B2 takes in candidates within 1 of a B1 pixel, dead ones too (a cosmic
+    // ray beside a star): dead candidates within 1 of a live one are
+    // evaluated with the live ones
+    {
+      const uint32_t up = wt ? s.word(kBitDead, wr, ww) & s.word(kBitD1, wr, ww) : 0u;
+      __syncthreads();
+      if (up) {
+        atomicOr(&s.word(kBitCd, wr, ww), up);
+        for (uint32_t d = up; d; d &= d - 1) s.mark_near(wr, 32 * ww + __ffs((int)d) - 1);
+      }
+    }
+    bool marked = true;
+#pragma unroll 1
+    for (int b0 = 4; b0 < RH - 4;) {
+      const bool ok = detect(b0, min(b0 + rows, RH - 4), marked);
+      marked = false;
+      if (ok)
+        b0 += rows;
+      else
+        rows = max(kBand, rows / 4 * 2);
+    }
+  }
+
+  // ---- 5. growth
+  bool changed = false;
+  next_phase();
+  if (s.any_b1) {  // (uniform: written before a barrier, read after it)
+    if (tid == 0) s.cnt = 0u;
+    if (wt) {
+      uint32_t nw = 0u;
+      if (wr >= 6 && wr < RH - 6) {
+        // B2 of the rows above, of and below this one, each word with the
+        // last column of the word before it and the first of the one after
+        BitSpan b2 = {0u, 0u, 0u};
+        BitSpan x0 = s.span(kBitB1, wr - 2, ww), x1 = s.span(kBitB1, wr - 1, ww);
+#pragma unroll
+        for (int k = -1; k <= 1; ++k) {
+          const BitSpan x2 = s.span(kBitB1, wr + k + 1, ww), g = s.span(kBitG1, wr + k, ww);
+          const BitSpan v = x0 | x1 | x2;
+          b2 = b2 | BitSpan{(v.l | (v.l << 1) | (v.c << 31)) & g.l, span_dil<1>(v) & g.c,
+                            (v.r | (v.r >> 1) | (v.c >> 31)) & g.r};
+          x0 = x1;
+          x1 = x2;
+        }
+        const uint32_t b3 = span_dil<1>(b2) & s.word(kBitG2, wr, ww) & col_bits(ww, 6, RW - 6);
+        const uint32_t m = s.word(kBitM, wr, ww);
+        nw = b3 & ~m;
+        s.word(kBitM, wr, ww) = m | b3;
+        const uint32_t own = nw & col_bits(ww, HL, HL + TW_);
+        if (wr >= HL && wr < HL + TH && own) atomicAdd(&s.fresh, (unsigned int)__popc(own));
+      }
+      s.word(kBitCd, wr, ww) = nw;  // the new mask pixels
+    }
+    __syncthreads();
+    if (!inner) {  // the replacement's windows clamp on the frame too
+      uint32_t m = 0u;
+      if (wt) {
+        const int cr = clampi(ry0 + wr, h - 1) - ry0;
+        const uint32_t lo_out = col_bits(ww, 0, fc0), hi_out = col_bits(ww, fc1, RW);
+        m = s.word(kBitM, cr, ww) & ~(lo_out | hi_out);
+        if (lo_out && s.bit(kBitM, cr, fc0)) m |= lo_out;
+        if (hi_out && s.bit(kBitM, cr, fc1 - 1)) m |= hi_out;
+      }
+      __syncthreads();
+      if (wt) s.word(kBitM, wr, ww) = m;
+    }
+    // the tile's mask pixels: those within 2 of a new one are replaced anew,
+    // the others keep their value
+    uint32_t redo = 0u, keep = 0u;
+    if (wt && wr >= HL && wr < HL + TH && row_in(wr)) {
+      const uint32_t own = s.word(kBitM, wr, ww) & col_bits(ww, HL, min(HL + TW_, fc1));
+      if (own) {
+        BitSpan o = s.span(kBitCd, wr - 2, ww);
+#pragma unroll
+        for (int k = -1; k <= 2; ++k) o = o | s.span(kBitCd, wr + k, ww);
+        const uint32_t d = span_dil<2>(o);
+        redo = own & d;
+        keep = own & ~d;
+        if (redo) {
+          const int zy = wr < 2 * HL ? 0 : wr < TH ? 1 : 2;
+          const uint32_t z = ((redo & col_bits(ww, HL, 2 * HL)) ? 1u : 0u) |
+                             ((redo & col_bits(ww, 2 * HL, TW_)) ? 2u : 0u) |
+                             ((redo & col_bits(ww, TW_, TW_ + HL)) ? 4u : 0u);
+          atomicOr(&s.zones, z << (1 + 3 * zy));
+        }
+      }
+    }
+    const unsigned int nr = __popc(redo);
+    const unsigned int rbase = nr ? atomicAdd(&s.cnt, nr) : 0u;
+    __syncthreads();
+    const unsigned int nredo = s.cnt;
+    changed = nredo != 0u;  // (uniform)
+    float* vals = iter_values(f, plane ^ 1u);
+    if (changed) {
+      while (keep) {  // carried values, plane to plane
+        const int q = __ffs((int)keep) - 1 + 32 * ww;
+        keep &= keep - 1;
+        stg(vals, (int64_t)(ry0 + wr) * w + rx0 + q, s.c[wr][q]);
+      }
+    }
+    unsigned int unrep = 0;
+    for (unsigned int c0 = 0; c0 < nredo; c0 += ICAP) {
+      unsigned int at = rbase;
+      for (uint32_t bits = redo; bits; bits &= bits - 1) {
+        const int b = __ffs((int)bits) - 1;
+        if (at - c0 < (unsigned int)ICAP) s.lst[at - c0] = (uint16_t)(wr * RW + 32 * ww + b);
+        ++at;
+      }
+      __syncthreads();
+      const unsigned int n = min(nredo - c0, (unsigned int)ICAP);
+      for (unsigned int j0 = 0; j0 < n; j0 += NT) {
+        const unsigned int j = j0 + tid;
+        float out = 0.0f;
+        int r = 0, q = 0;
+        if (j < n) {
+          const int i = s.lst[j];
+          r = i / RW;
+          q = i - r * RW;
+          out = s.c[r][q];  // (no mask pixel's value is below s.mn: the patches count in it)
+          int v[25];
+          int cnt = 0;
+#pragma unroll
+          for (int a = 0; a < 5; ++a) {
+            // the window row's five mask bits, across a word boundary or not
+            const uint32_t* mw = &s.word(kBitM, r - 2 + a, (q - 2) >> 5);
+            const uint32_t bits = __builtin_amdgcn_alignbit(mw[1], mw[0], (q - 2) & 31);
+            cnt += 5 - __popc(bits & 31u);
+#pragma unroll
+            for (int b = 0; b < 5; ++b)
+              v[a * 5 + b] = __float_as_int(s.c[r - 2 + a][q - 2 + b]);
+            if (!nonneg) {
+#pragma unroll
+              for (int b = 0; b < 5; ++b) v[a * 5 + b] ^= (v[a * 5 + b] >> 31) & 0x7fffffff;
+            }
+#pragma unroll
+            for (int b = 0; b < 5; ++b) v[a * 5 + b] = ((bits >> b) & 1u) ? KEY_EXCLUDED : v[a * 5 + b];
+          }
+          if (cnt > 0) {
+            int srt[13];
+            sort25_lo13(v, srt);  // ranks 0..12: the lower median of cnt <= 25 values
+            const int rk = (cnt - 1) >> 1;
+            int sel = srt[0];
+#pragma unroll
+            for (int k = 1; k < 13; ++k) sel = (rk == k) ? srt[k] : sel;
+            out = funkey(sel);
+          } else {
+            // counted when the previous mask still left an un-flagged cell in
+            // the window (the pixel itself among them): one is new
+            bool first = false;
+            for (int a = 0; a < 5; ++a)
+              for (int b = 0; b < 5; ++b)
+                first |= s.bit(kBitCd, clampi(ry0 + r - 2 + a, h - 1) - ry0,
+                               clampi(rx0 + q - 2 + b, w - 1) - rx0);
+            unrep += first ? 1u : 0u;
+          }
+          const int64_t gi = (int64_t)(ry0 + r) * w + rx0 + q;
+          stg(vals, gi, out);
+          if (it > 0) {
+            stg(f.clean, gi, out);
+            stg(f.out_mask, gi, (uint8_t)1);
+          }
+        }
+        if (it == 0) {  // the whole tile is stored below, from LDS
+          __syncthreads();
+          if (j < n) s.c[r][q] = out;
+          __syncthreads();
+        }
+      }
+      __syncthreads();  // the list is rebuilt
+    }
+    if (unrep) atomicAdd(&s.unrep, unrep);
+    __syncthreads();
+    if (tid == 0) {
+      if (s.fresh) atom_add(f.n_new + it, (unsigned long long)s.fresh);
+      if (s.unrep) atom_add(f.n_new + f.niter, (unsigned long long)s.unrep);
+    }
+  }
+
+  // ---- state, mask bits, and in iteration 0 the whole tile's outputs
+  const bool write = changed || it == 0;
+  next_phase();
+  if (tid == 0) stg(iter_state(f, it), tile, write ? ((plane ^ 1u) | (changed ? s.zones : 0u)) : plane);
+  if (!write) return;
+  if (tid < TH && y0 + tid < h) {
+    const uint32_t* m = &s.word(kBitM, tid + HL, 0);
+    uint64_t word = (m[0] >> 8) | (m[1] << 24);
+    if (TW_ == 64) word |= (uint64_t)((m[1] >> 8) | (m[2] << 24)) << 32;
+    if (w - x0 < 64) word &= (1ull << (w - x0)) - 1ull;  // pixels of the frame only
+    uint64_t* p = (plane ^ 1u) ? f.mbits[1] : f.mbits[0];
+    if (TW_ == 64)
+      stg(p, (int64_t)(y0 + tid) * f.wpr + tx, word);
+    else
+      stg(reinterpret_cast<uint32_t*>(p), (int64_t)(y0 + tid) * f.wpr * 2 + tx, (uint32_t)word);
+  }
+  if (it > 0) return;
+  if (y0 + TH <= h && x0 + TW_ <= w) {
+    constexpr int C4 = TW_ / 4, RP = NT / C4;  // C4 threads per row, RP rows at a time
+    static_assert(TH % RP == 0, "whole passes");
+    const int r0 = tid / C4, q0 = 4 * (tid - r0 * C4);
+    float* cl = f.clean + (int64_t)y0 * w + x0;
+#pragma unroll
+    for (int k = 0; k < TH / RP; ++k) {
+      const float4 v = *reinterpret_cast<const float4*>(&s.c[r0 + k * RP + HL][q0 + HL]);
+      *(__attribute__((address_space(1))) f4u*)(cl + (uint32_t)((r0 + k * RP) * w + q0)) = f4u{v.x, v.y, v.z, v.w};
+    }
+    // 16 mask bytes per thread, wherever the row starts
+    constexpr int M16 = TW_ / 16;
+    typedef uint32_t u4u __attribute__((ext_vector_type(4), aligned(1)));
+    if (tid < TH * M16) {
+      const int r = tid / M16, q = 16 * (tid - r * M16);
+      const uint32_t* m = &s.word(kBitM, r + HL, (HL + q) >> 5);
+      const uint32_t b = __builtin_amdgcn_alignbit(m[1], m[0], (HL + q) & 31);
+      *(__attribute__((address_space(1))) u4u*)(f.out_mask + (int64_t)(y0 + r) * w + x0 + q) =
+          u4u{spread4(b & 15u), spread4((b >> 4) & 15u), spread4((b >> 8) & 15u), spread4((b >> 12) & 15u)};
+    }
+  } else {
+    for (int i = tid; i < TH * TW_; i += NT) {
+      const int r = i / TW_, q = i - r * TW_;
+      if (y0 + r >= h || x0 + q >= w) continue;
+      const int64_t gi = (int64_t)(y0 + r) * w + x0 + q;
+      stg(f.clean, gi, s.c[r + HL][q + HL]);
+      stg(f.out_mask, gi, (uint8_t)(s.bit(kBitM, r + HL, q + HL) ? 1 : 0));
+    }
+  }
+}
+
+// A block's share of iteration it: n tiles from t0 on.
+template <int TH, int TW_>
+__device__ __forceinline__ void tiles_iter(const FrameDev& f, int it, int t0, int n, SmemIter<TH, TW_>& s) {
+  if (stopped(f, it)) return;  // the outputs already hold the result
+  unsigned long long act = n >= 64 ? ~0ull : (1ull << n) - 1ull;
+  // a new gain changes the noise model everywhere
+  if (it > 0 && !f.est_gain) act = iter_active<TH, TW_>(f, it, t0, n);
+#pragma unroll 1
+  while (act) {
+    const int k = __ffsll((long long)act) - 1;
+    act &= act - 1;
+    tile_iter<TH, TW_>(f, it, t0 + k, s);
+    if (act) __syncthreads();  // the next tile reuses the LDS
+  }
+}
+
+}  // namespace lac

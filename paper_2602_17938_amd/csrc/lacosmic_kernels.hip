@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "lacosmic_gain.h"
+#include "lacosmic_iter.h"
 #include "lacosmic_launch.h"
 #include "lacosmic_small.h"
 #include "lacosmic_tiles.h"
@@ -101,6 +102,58 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(const FrameDev* __restr
   __shared__ SmemFused s;
   const FrameDev f = *fp;
   tile_fused<kFusedThreads>(f, it, xcd_remap(blockIdx.x, gridDim.x), s);
+}
+
+// One whole iteration of a frame, `chunk` consecutive TH x TW_ output tiles
+// per block (consecutive blocks on one XCD: their regions overlap).
+template <int TH, int TW_>
+__global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter(const FrameDev* __restrict__ fp, int it,
+                                                          int ntiles, int chunk) {
+  __shared__ SmemIter<TH, TW_> s;
+  const FrameDev f = *fp;
+  const int t0 = xcd_remap(blockIdx.x, gridDim.x) * chunk;
+  tiles_iter<TH, TW_>(f, it, t0, min(chunk, ntiles - t0), s);
+}
+
+// Index of the last frame whose first tile is at or before tile t (base: the
+// frames' first tiles, ascending), by every wave on its own: each round
+// narrows the range 64-fold with one load.
+__device__ __forceinline__ int frame_of_wave(const int* base, int nframes, int t) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, len = nframes;
+  while (len > 1) {
+    const int step = (len + 63) >> 6;
+    const int at = lane * step;
+    const bool le = at < len && ldg(base, lo + at) <= t;
+    const int c = __popcll(__ballot(le)) - 1;  // lane 0 holds: base[lo] <= t
+    lo += c * step;
+    len = min(step, len - c * step);
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// The same over the tiles of many frames (tile_base: prefix sums of their
+// TH x TW_ tile counts).  it < 0: each frame runs its own FrameDev::it.
+template <int TH, int TW_>
+__global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(const FrameDev* __restrict__ frames,
+                                                                 const int* tile_base, int nframes, int it,
+                                                                 int chunk) {
+  __shared__ SmemIter<TH, TW_> s;
+  const int total = ldg(tile_base, nframes);
+  int t = xcd_remap(blockIdx.x, gridDim.x) * chunk;
+  const int t1 = min(t + chunk, total);
+  int fi = frame_of_wave(tile_base, nframes, t);
+#pragma unroll 1
+  while (t < t1) {  // a run of tiles of one frame at a time
+    const int b0 = __builtin_amdgcn_readfirstlane(ldg(tile_base, fi));
+    const int b1 = __builtin_amdgcn_readfirstlane(ldg(tile_base, fi + 1));
+    const FrameDev f = frames[fi];
+    const int n = min(t1, b1) - t;
+    tiles_iter<TH, TW_>(f, it >= 0 ? it : f.it, t - b0, n, s);
+    t += n;
+    ++fi;
+    if (t < t1) __syncthreads();
+  }
 }
 
 // Stores a frame record (a kernel argument) in device memory.
@@ -324,7 +377,7 @@ __global__ void k_batch_init(const FrameDev* frames, int nframes, unsigned int* 
     const FrameDev& f = frames[fi];
     for (int i = threadIdx.x; i <= f.niter; i += blockDim.x) f.n_new[i] = 0ull;
     for (int i = threadIdx.x; i < kCntPerIter * f.niter; i += blockDim.x) f.counts[i] = 0u;
-    const int nst = ((f.h + kBStrip - 1) / kBStrip) * strip_ncols(f.wpr);
+    const int nst = f.fused == kFusedTiles ? 0 : ((f.h + kBStrip - 1) / kBStrip) * strip_ncols(f.wpr);
     for (int i = threadIdx.x; i < nst; i += blockDim.x) {
       f.b1s[i] = 0;
       f.bq[i] = 0;
@@ -416,6 +469,17 @@ static void sparse_launch(const FrameDev* fd, int it, unsigned ns, hipStream_t s
   k_sparse_frame<WHICH><<<ns, 256, 0, st>>>(fd, it);
 }
 
+// Tiles per block of a one-launch iteration.  Iteration 0 works on every
+// tile, iteration 1 on nearly every one (most hold a pixel that iteration 0
+// changed): one block each, scheduled as they finish.  Later ones skip most
+// tiles, and a block that only finds that out still takes its turn on a CU
+// (three fit at once): up to 8 tiles per block, looked at side by side, but
+// at least two blocks per CU slot.
+static int iter_chunk(int tiles, int it) {
+  if (it <= 1) return 1;
+  return std::max(1, std::min(8, tiles / (6 * (sparse_blocks() / 8))));
+}
+
 // One iteration: grid sizes from the host copy f, the kernels read the
 // device copy fd.
 template <int TH, int NT>
@@ -431,6 +495,17 @@ static hipError_t frame_iter_t(const FrameDev& f, const FrameDev* fd, int it, hi
     if (f.est_gain) {
       const hipError_t e = launch_gain(fd, 1, it, gain_blocks(px), st);
       if (e != hipSuccess) return e;
+    }
+    if (f.fused == kFusedTiles) {
+      const int shape = iter_shape(px);
+      const int nt = (int)iter_tiles(f.h, f.w, shape);
+      const int chunk = f.est_gain ? 1 : iter_chunk(nt, it);
+      const unsigned nb = (unsigned)((nt + chunk - 1) / chunk);
+      if (shape == kIterSmall)
+        k_iter<32, 32><<<nb, kIterThreads, 0, st>>>(fd, it, nt, chunk);
+      else
+        k_iter<64, 64><<<nb, kIterThreads, 0, st>>>(fd, it, nt, chunk);
+      return hipGetLastError();
     }
     const unsigned nt = (unsigned)(((f.h + FT - 1) / FT) * ((f.w + FT - 1) / FT));
     k_fused<<<nt, kFusedThreads, 0, st>>>(fd, it);
@@ -565,6 +640,24 @@ hipError_t launch_queue_pass(const QueueArgs& a, int pass, int it, int cfg, int 
     case 2: return queue_pass_t<8, 128>(a, pass, it, mode, st);
     default: return queue_pass_t<16, 256>(a, pass, it, mode, st);
   }
+}
+
+int iter_shape(int64_t pixels) { return pixels <= kIterSmallPx ? kIterSmall : kIterLarge; }
+
+int64_t iter_tiles(int64_t h, int64_t w, int shape) {
+  const int64_t e = shape == kIterSmall ? 32 : 64;
+  return ((h + e - 1) / e) * ((w + e - 1) / e);
+}
+
+hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, hipStream_t st) {
+  if (a.blocks <= 0) return hipSuccess;
+  const int chunk = iter_chunk(a.blocks, it);
+  const unsigned nb = (unsigned)((a.blocks + chunk - 1) / chunk);
+  if (shape == kIterSmall)
+    k_iter_frames<32, 32><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, chunk);
+  else
+    k_iter_frames<64, 64><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, chunk);
+  return hipGetLastError();
 }
 
 // Counts the binary32 inputs with bit patterns in [lo, hi] where sqrt_rn_fast

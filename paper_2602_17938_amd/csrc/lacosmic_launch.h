@@ -62,6 +62,14 @@ inline bool pass_runs(int pass, int it, int niter, bool est = false) {
   }
 }
 
+// Tile shapes of the one-launch iterations (lacosmic_iter.h): 32 x 32 output
+// pixels for runs of at most kIterSmallPx pixels in all, whose 64 x 64 tiles
+// would leave CUs idle, else 64 x 64.
+constexpr int kIterSmall = 0, kIterLarge = 1;
+constexpr int64_t kIterSmallPx = int64_t(1) << 20;
+int iter_shape(int64_t pixels);
+int64_t iter_tiles(int64_t h, int64_t w, int shape);
+
 // Zero one frame's niter + 1 counters (per-iteration new pixels, then the
 // unreplaced pixels), list lengths, status word and nstamps strip stamps.
 hipError_t launch_init(unsigned long long* n_new, int niter, int* status, unsigned int* counts,
@@ -108,6 +116,9 @@ hipError_t launch_queue_init(const QueueArgs& a, int ncursors, int zero_counters
 // frame's iteration does nothing for it).
 hipError_t launch_queue_pass(const QueueArgs& a, int pass, int it, int cfg, int mode,
                              hipStream_t st);
+// One iteration of every frame of a table in one launch (lacosmic_iter.h):
+// a.tile_base and a.blocks count the shape's tiles; it as above.
+hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, hipStream_t st);
 // Gain estimate of iteration it (it < 0: each frame's own FrameDev::it) for
 // the frames of a table (one frame: its record) that estimate their gain:
 // a reset, then up to 5 sigma-clipping rounds of three passes and the final

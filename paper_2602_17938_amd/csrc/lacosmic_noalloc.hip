@@ -67,7 +67,7 @@ extern "C" int lacosmic_run_noalloc(const float* img, int64_t h, int64_t w,
     if (!ws) return LACOSMIC_EHIP;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);  // NULL: the legacy null stream
     FrameDev f = make_frame(img, h, w, *p, out_mask, out_clean, ws, L, kDefaultTileCfg);
-    f.fused = use_fused(h, w, *p) ? 1 : 0;
+    f.fused = fused_form(h, w, *p, false);
     FrameDev* fd = reinterpret_cast<FrameDev*>(ws + L.rec);
     if (launch_put_frame(f, fd, s) != hipSuccess ||
         launch_init(f.n_new, f.niter, f.status, f.counts, f.b1s, (int64_t)L.nstamps, s) !=

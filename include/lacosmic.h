@@ -195,10 +195,12 @@ typedef struct {
 } lacosmic_ws_layout;
 int lacosmic_workspace_layout(int64_t h, int64_t w, lacosmic_ws_layout* out);
 
-/* Many frames of different sizes, one launch per pass over the tiles of all
- * frames of a group (a persistent launch pulling tiles from a shared queue, or
- * one block per tile); the frames are split into groups of about equal pixel
- * counts whose chains of launches run concurrently.  Tile shape, launch form
+/* Many frames of different sizes.  A batch of at most 2^27 pixels runs one
+ * launch per iteration over the tiles of all frames.  A larger one runs one
+ * launch per pass over the tiles of all frames of a group (a persistent launch
+ * pulling tiles from a shared queue, or one block per tile); the frames are
+ * split into groups of about equal pixel counts whose chains of launches run
+ * concurrently.  Tile shape, launch form
  * and group count are the fastest on the first call for the batch shape; the
  * niter loop is recorded once per batch shape as a HIP graph and replayed.  imgs, hs, ws, out_masks, out_cleans are HOST arrays of n
  * entries (the pointers they hold are device pointers); p holds n parameter
@@ -210,8 +212,11 @@ int lacosmic_run_batch(int32_t n, const float* const* imgs, const int64_t* hs, c
                        float* const* out_cleans, void* hip_stream);
 
 /* Index of the tile shape (see lacosmic_get_tile_shape) the batched path
- * chose, by timing, for the most recent batch shape on the current device;
- * -1 before the first batch.  LACOSMIC_AUTOTUNE=0 disables the timing. */
+ * chose, by timing, for the most recent batch shape on the current device
+ * (one launch per iteration: the single-frame passes' shape, which it does not
+ * use); -1 before the first batch.  LACOSMIC_AUTOTUNE=0 disables the timing;
+ * LACOSMIC_BATCH_PLAN="cfg,mode[,groups]" pins the launches per pass and
+ * their plan at any size. */
 int lacosmic_batch_tile_shape(void);
 /* Launch form the batched path chose with it: 0 = one persistent launch per
  * pass pulling tiles from a queue, 1 = one block per tile; -1 before the

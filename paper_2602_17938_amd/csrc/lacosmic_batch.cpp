@@ -1,7 +1,9 @@
-// Batched path: many frames of mixed sizes through one persistent tile-queue
-// launch per pass, the whole niter loop recorded once per batch shape as a
-// HIP graph and replayed; the tile shape is picked by timing the candidates
-// on the first call for a batch shape.
+// Batched path: many frames of mixed sizes together, in one of two forms.
+// Batches of at most kIterBatchPx pixels run one launch per iteration over the
+// tiles of all frames (lacosmic_iter.h).  Larger ones run one launch per pass,
+// the whole niter loop recorded once per batch shape as a HIP graph and
+// replayed; tile shape, launch form and group count are picked by timing the
+// candidates on the first call for a batch shape.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,6 +26,14 @@ static size_t counter_stride(int niter) {
   return (size_t)niter + 2 + ((size_t)kCntPerIter * niter + 1) / 2;
 }
 
+// Pixels up to which a batch runs one launch per iteration.  The passes'
+// chain of about seven launches per iteration costs about 0.6 ms whatever the
+// batch (four iterations); per pixel it is the cheaper form, its sparse passes
+// running on full waves over all frames' lists.  Measured, tiles against
+// passes: 9.3 Mpx of cutouts 0.56 / 0.94 ms, 35 Mpx 0.56 / 0.78, 67 Mpx 0.92 /
+// 1.10, 100 Mpx 1.28 / 1.40, 1028 Mpx 11.3 / 8.5.
+constexpr int64_t kIterBatchPx = int64_t(1) << 27;
+
 // Frames are split into groups of about equal pixel counts; each group's
 // passes form their own chain of launches, on its own stream inside the
 // recorded graph, so one group's latency-bound passes and launch tails
@@ -33,10 +43,13 @@ struct BatchPlan {
   // signature (est: some frame estimates its gain, so every iteration
   // launches the gain passes and A1)
   int n = 0, niter = 0, early = 0, est = 0, cfg = 0, mode = kModeQueue;
+  bool tiles = false;           // one launch per iteration, of tile shape `shape`
+  int shape = 0;
   std::vector<int64_t> hs, ws;  // in the caller's order
   // frame groups: table entry t holds the caller's frame order[t]; group g is
   // entries [gstart[g], gstart[g + 1]); its tile bases start at goff[g] in
-  // tile_base_dev (pass-A tiles, then pass-B tiles, (ng + 1) each)
+  // tile_base_dev (pass-A tiles, then pass-B tiles, (ng + 1) each; with
+  // `tiles` the iterations' tiles, total_a counting them, and no pass-B ones)
   int ngroups = 1;
   std::vector<int> order, gstart, goff, total_a, total_b;
   std::vector<int> gain_nbx;  // per group: blocks per frame of the gain passes
@@ -45,6 +58,8 @@ struct BatchPlan {
   FrameDev* frames_dev = nullptr;   // frame table
   int* tile_base_dev = nullptr;
   unsigned int* cursors_dev = nullptr;  // ncur() per group
+  int* lists_dev = nullptr;  // `tiles`: per group two lists of its tiles (at 2 x lists_off)
+  std::vector<int64_t> lists_off;
   unsigned long long* counters_dev = nullptr;
   std::vector<WsLayout> lay;  // per table entry
   std::vector<size_t> ws_off;
@@ -78,6 +93,7 @@ struct BatchPlan {
     if (frames_dev) (void)hipFree(frames_dev);
     if (tile_base_dev) (void)hipFree(tile_base_dev);
     if (cursors_dev) (void)hipFree(cursors_dev);
+    if (lists_dev) (void)hipFree(lists_dev);
     if (counters_dev) (void)hipFree(counters_dev);
   }
   bool same(int n_, const int64_t* h_, const int64_t* w_, int niter_, int early_, int est_) const {
@@ -123,6 +139,7 @@ static void fill_table(BatchPlan& P, const float* const* imgs, const lacosmic_pa
     FrameDev f = make_frame(imgs[i], P.hs[i], P.ws[i], p[i], out_masks[i], out_cleans[i],
                             P.ws_dev + P.ws_off[t], P.lay[t], P.cfg);
     unsigned long long* ctr = P.counters_dev + counter_stride(P.niter) * (size_t)t;
+    f.fused = P.tiles ? kFusedTiles : kFusedOff;
     f.n_new = ctr;
     f.status = reinterpret_cast<int*>(ctr + P.niter + 1);
     f.counts = reinterpret_cast<unsigned int*>(ctr + P.niter + 2);
@@ -156,8 +173,21 @@ static hipError_t enqueue_plan(BatchPlan& P, hipStream_t s, bool marks) {
     const int* tb = P.tile_base_dev + P.goff[g];
     QueueArgs a{P.frames_dev + P.gstart[g], tb, tb + (ng + 1), ng,
                 P.cursors_dev + (size_t)P.ncur() * g, 0, 0};
+    if (P.tiles) a.lists = P.lists_dev + 2 * P.lists_off[g];
     if (marks) e = hipEventRecord(P.marks[g * per], s);
-    for (int it = 0; it < niter && e == hipSuccess; ++it) {
+    // one launch per iteration: its time reads as A1's
+    for (int it = 0; P.tiles && it < niter && e == hipSuccess; ++it) {
+      for (int pass = 0; pass < kPassesPerIter && e == hipSuccess; ++pass) {
+        a.blocks = pass == kPassGain ? P.gain_nbx[g] : P.total_a[g];
+        if (pass == kPassGain && P.est)
+          e = launch_queue_pass(a, pass, it, P.cfg, P.mode, st);
+        else if (pass == kPassA1)
+          e = launch_iter_frames(a, it, P.shape, P.est != 0, st);
+        if (e == hipSuccess && marks)
+          e = hipEventRecord(P.marks[g * per + 1 + kPassesPerIter * it + pass], s);
+      }
+    }
+    for (int it = 0; !P.tiles && it < niter && e == hipSuccess; ++it) {
       for (int pass = 0; pass < kPassesPerIter && e == hipSuccess; ++pass) {
         if (pass_runs(pass, it, niter, P.est != 0)) {
           const int slot = dense_slot(pass);
@@ -229,13 +259,18 @@ static int pinned_groups() {
 }
 
 static int build_plan(BatchPlan& P, int n, const int64_t* hs, const int64_t* ws, int niter,
-                      int early, int est, int cfg, int mode, int groups, hipStream_t cap) {
+                      int early, int est, int cfg, int mode, int groups, bool tiles,
+                      hipStream_t cap) {
   P.n = n;
   P.niter = niter;
   P.early = early;
   P.est = est;
   P.cfg = cfg;
   P.mode = mode;
+  P.tiles = tiles;
+  int64_t pixels = 0;
+  for (int i = 0; i < n; ++i) pixels += hs[i] * ws[i];
+  P.shape = iter_shape(pixels);
   P.hs.assign(hs, hs + n);
   P.ws.assign(ws, ws + n);
   make_groups(P, groups);
@@ -259,14 +294,15 @@ static int build_plan(BatchPlan& P, int n, const int64_t* hs, const int64_t* ws,
       P.lay[t] = ws_layout(hs[i], ws[i]);
       P.ws_off[t] = total;
       total += P.lay[t].total;
-      const int64_t tiles = ((ws[i] + ts.tw - 1) / ts.tw) * ((hs[i] + ts.th - 1) / ts.th);
+      const int64_t tiles_a = P.tiles ? iter_tiles(hs[i], ws[i], P.shape)
+                                      : ((ws[i] + ts.tw - 1) / ts.tw) * ((hs[i] + ts.th - 1) / ts.th);
       const int64_t band = (int64_t)kBStrip * kBWaves;
       const int64_t tiles_b =
           ((hs[i] + band - 1) / band) * strip_ncols((int)((ws[i] + 63) / 64));
-      if ((int64_t)base[o + k] + tiles > 0x7fffffff ||
+      if ((int64_t)base[o + k] + tiles_a > 0x7fffffff ||
           (int64_t)base[o + ng + 1 + k] + tiles_b > 0x7fffffff)
         return LACOSMIC_EINVAL;
-      base[o + k + 1] = base[o + k] + (int)tiles;
+      base[o + k + 1] = base[o + k] + (int)tiles_a;
       base[o + ng + 1 + k + 1] = base[o + ng + 1 + k] + (int)tiles_b;
     }
     P.total_a[g] = base[o + ng];
@@ -279,6 +315,14 @@ static int build_plan(BatchPlan& P, int n, const int64_t* hs, const int64_t* ws,
     P.gain_nbx[g] = gain_blocks(biggest);
   }
   const int ncur = P.ncur() * G;
+  if (P.tiles) {
+    int64_t all_tiles = 0;
+    for (int g = 0; g < G; ++g) {
+      P.lists_off.push_back(all_tiles);
+      all_tiles += P.total_a[g];
+    }
+    if (hipMalloc(&P.lists_dev, sizeof(int) * 2 * all_tiles) != hipSuccess) return LACOSMIC_ENOMEM;
+  }
   if (hipMalloc(&P.ws_dev, total) != hipSuccess ||
       hipMalloc(&P.frames_dev, sizeof(FrameDev) * n) != hipSuccess ||
       hipMalloc(&P.tile_base_dev, sizeof(int) * base.size()) != hipSuccess ||
@@ -293,10 +337,8 @@ static int build_plan(BatchPlan& P, int n, const int64_t* hs, const int64_t* ws,
   if (hipMemcpy(P.tile_base_dev, base.data(), sizeof(int) * base.size(),
                 hipMemcpyHostToDevice) != hipSuccess)
     return LACOSMIC_EHIP;
-  for (int pass : {kPassA1, kPassSC, kPassB, kPassOut}) P.blocks[dense_slot(pass)] = queue_blocks(cfg, pass);
-  P.marks.resize((size_t)G * (kPassesPerIter * niter + 1), nullptr);
-  for (auto& ev : P.marks)
-    if (hipEventCreate(&ev) != hipSuccess) return LACOSMIC_EHIP;
+  if (!P.tiles)
+    for (int pass : {kPassA1, kPassSC, kPassB, kPassOut}) P.blocks[dense_slot(pass)] = queue_blocks(cfg, pass);
   P.gstream.resize(G - 1, nullptr);
   P.fork.resize(1, nullptr);
   P.join.resize(G - 1, nullptr);
@@ -306,6 +348,8 @@ static int build_plan(BatchPlan& P, int n, const int64_t* hs, const int64_t* ws,
   for (auto* v : {&P.fork, &P.join, &P.a1_done})
     for (auto& ev : *v)
       if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return LACOSMIC_EHIP;
+
+  if (P.tiles) return LACOSMIC_OK;  // few launches: enqueued at each call
 
   // Record the whole run once: counter/cursor reset, then the passes of each
   // iteration.  Only kernel nodes: the cursors are cleared by a kernel, never
@@ -334,7 +378,8 @@ static int launch_plan(BatchPlan& P, const float* const* imgs, const lacosmic_pa
   if (hipStreamWaitEvent(s, P.run_done, 0) != hipSuccess ||
       hipMemcpyAsync(P.frames_dev, P.frames_pin, sizeof(FrameDev) * P.n, hipMemcpyHostToDevice,
                      s) != hipSuccess ||
-      hipEventRecord(P.table_done, s) != hipSuccess || hipGraphLaunch(P.exec, s) != hipSuccess ||
+      hipEventRecord(P.table_done, s) != hipSuccess ||
+      (P.tiles ? enqueue_plan(P, s, false) : hipGraphLaunch(P.exec, s)) != hipSuccess ||
       hipEventRecord(P.run_done, s) != hipSuccess)
     return LACOSMIC_EHIP;
   return LACOSMIC_OK;
@@ -416,7 +461,7 @@ static int autotune(DevCtx* c, int n, const float* const* imgs, const int64_t* h
     if (std::find(tried.begin(), tried.end(), key) != tried.end()) continue;
     tried.push_back(key);
     BatchPlan* P = new BatchPlan();
-    rc = build_plan(*P, n, hs, ws, niter, early, est, cfg, mode, groups, c->stream);
+    rc = build_plan(*P, n, hs, ws, niter, early, est, cfg, mode, groups, false, c->stream);
     // rep 0 warms up; the plan's time is the best of the next three runs (an
     // untimed plan counts as 0 and is kept)
     float ms = tune ? 1e29f : 0.0f;
@@ -516,7 +561,17 @@ extern "C" int lacosmic_run_batch(int32_t n, const float* const* imgs, const int
         B->plan = nullptr;
       }
       BatchPlan* P = nullptr;
-      if (cfg < 0) {
+      int64_t pixels = 0;
+      for (int i = 0; i < n; ++i) pixels += hs[i] * ws[i];
+      if (pixels <= kIterBatchPx && !std::getenv("LACOSMIC_BATCH_PLAN")) {
+        P = new BatchPlan();
+        const int rc = build_plan(*P, n, hs, ws, niter, early, est, c->cfg, kModeGrid,
+                                  std::max(1, pinned_groups()), true, c->stream);
+        if (rc) {
+          delete P;
+          return rc;
+        }
+      } else if (cfg < 0) {
         const int rc =
             autotune(c, n, imgs, hs, ws, p, out_masks, out_cleans, niter, early, est, s, &P);
         if (rc) return rc;
@@ -524,7 +579,7 @@ extern "C" int lacosmic_run_batch(int32_t n, const float* const* imgs, const int
       } else {
         P = new BatchPlan();
         const int rc = build_plan(*P, n, hs, ws, niter, early, est, (cfg >> 1) & 127, cfg & 1,
-                                  cfg >> 8, c->stream);
+                                  cfg >> 8, false, c->stream);
         if (rc) {
           delete P;
           return rc;
@@ -554,6 +609,11 @@ extern "C" int lacosmic_batch_pass_ms(float* ms, int32_t n, void* hip_stream) {
     if (!c->batch || !c->batch->plan) return 0;
     BatchPlan& P = *c->batch->plan;
     hipStream_t s = hip_stream ? static_cast<hipStream_t>(hip_stream) : c->stream_after_null();
+    if (P.marks.empty()) {
+      P.marks.resize((size_t)P.ngroups * (kPassesPerIter * P.niter + 1), nullptr);
+      for (auto& ev : P.marks)
+        if (hipEventCreate(&ev) != hipSuccess) return LACOSMIC_EHIP;
+    }
     if (!s || hipStreamWaitEvent(s, P.run_done, 0) != hipSuccess ||
         enqueue_plan(P, s, true) != hipSuccess || hipEventRecord(P.run_done, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)

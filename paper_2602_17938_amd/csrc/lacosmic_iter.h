@@ -34,10 +34,10 @@
 //      pixels within 2 of a new one) and their values, on bit rows.
 //
 // A tile whose region no value or mask bit changed in during the previous
-// iteration would repeat that iteration's result: it is skipped.  Each tile
-// records which of its 3x3 zones (8 pixels along the edges, and the middle)
-// held a change, and in which of the two mask and value planes its state
-// lies; like the planes, the records alternate between two arrays.
+// iteration would repeat that iteration's result: it is skipped.  A tile that
+// changes something stamps the tiles whose regions hold it for the next
+// iteration, and the first to stamp one appends it to that iteration's list.
+// (Iteration 1 works on every tile: nearly all hold a change of iteration 0.)
 //
 // Every value that decides anything is computed by the expressions of the
 // sparse path, so the results are the same bit for bit.
@@ -68,13 +68,24 @@ constexpr int kIterHalo = 8;     // the iteration's dependency radius
 constexpr int kIterThreads = 256;
 constexpr int kIterWaves = 4;    // waves per SIMD the launch bounds ask for (blocks per CU, with its LDS)
 
-// Tile state word of one iteration: bit 0, the plane (of two) that holds the
-// tile's mask bits and values; bit 1 + 3 * zy + zx, zone (zy, zx) of the tile
-// held a changed value or mask bit.
-
-__device__ __forceinline__ uint32_t* iter_state(const FrameDev& f, int it) {
-  return reinterpret_cast<uint32_t*>((it & 1) ? f.rs : f.dirty);
+// State word of a tile: bit 0, the plane (of two) that holds its mask bits
+// and values; above it, it + 1 for the iteration `it` that wrote them.  A
+// block that finds a neighbour written in its own iteration knows the plane
+// before: the other one, which the neighbour does not touch.  Stamp word of a
+// tile for iteration it, in one of two arrays used in turn: it + 1 if that
+// iteration has work for it.
+__device__ __forceinline__ uint32_t* iter_state(const FrameDev& f) {
+  return reinterpret_cast<uint32_t*>(f.dirty);
 }
+__device__ __forceinline__ uint32_t* iter_stamp(const FrameDev& f, int it) {
+  return reinterpret_cast<uint32_t*>((it & 1) ? f.rs : f.r4);
+}
+// The next iteration's list of tiles.
+struct IterList {
+  int* list;            // null: stamps only
+  unsigned int* count;  // its length so far
+  int base;             // added to the frame's tile index
+};
 __device__ __forceinline__ float* iter_values(const FrameDev& f, uint32_t plane) {
   return reinterpret_cast<float*>(plane ? f.conf : f.list);
 }
@@ -198,7 +209,8 @@ struct alignas(16) SmemIter {
   QIndex qmap[QR * QC];    // a block's index in s4, by position
   float wmin[kIterThreads / 64], wmax[kIterThreads / 64];
   float mn, nmin, thr;  // the region's smallest value, the noise there, the candidates' bound
-  unsigned int cnt, nq, n2, fresh, unrep, zones;
+  unsigned int cnt, nq, n2, fresh, unrep;
+  unsigned int zones;  // bit 3 zy + zx: 3x3 zones of the tile (8 pixels along the edges) with a change
   int any_b1, live;
   __device__ __forceinline__ static int at(int r, int ww) { return (r - BR0) * (NW + 1) + 1 + ww; }
   __device__ __forceinline__ BitSpan span(int plane, int r, int ww) const {
@@ -450,47 +462,18 @@ struct IterGrid {
   int tiles_x, tiles_y;
   __device__ __forceinline__ explicit IterGrid(const FrameDev& f)
       : tiles_x((f.w + TW_ - 1) / TW_), tiles_y((f.h + TH - 1) / TH) {}
-  // State after the previous iteration of neighbour k (0 .. 8, row-major) of
-  // tile (ty, tx); 0 outside the frame.
-  __device__ __forceinline__ uint32_t state(const uint32_t* prev, int ty, int tx, int k) const {
+  // Index of neighbour k (0 .. 8, row-major) of tile (ty, tx), or -1.
+  __device__ __forceinline__ int neighbour(int ty, int tx, int k) const {
     const int qy = ty + k / 3 - 1, qx = tx + k % 3 - 1;
-    const bool in = qy >= 0 && qy < tiles_y && qx >= 0 && qx < tiles_x;
-    const uint32_t v = ldg(prev, in ? qy * tiles_x + qx : ty * tiles_x + tx);
-    return in ? v : 0u;
+    return qy >= 0 && qy < tiles_y && qx >= 0 && qx < tiles_x ? qy * tiles_x + qx : -1;
   }
 };
-
-// Of tiles t0 .. t0 + n - 1 (n <= 64), those iteration it >= 1 has work for:
-// a value or mask bit changed within their region in the previous iteration.
-// The others' state carries over.  Every wave of the block gets the same set.
-template <int TH, int TW_>
-__device__ __forceinline__ unsigned long long iter_active(const FrameDev& f, int it, int t0, int n) {
-  const int lane = threadIdx.x & 63;
-  const IterGrid<TH, TW_> g(f);
-  bool act = false;
-  if (lane < n) {
-    const uint32_t* prev = iter_state(f, it - 1);
-    const int t = t0 + lane, ty = t / g.tiles_x, tx = t - ty * g.tiles_x;
-    uint32_t st[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) st[k] = g.state(prev, ty, tx, k);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      // zones of that tile the region overlaps: all of them (the tile
-      // itself), else its edge towards this tile
-      const uint32_t zr = k < 3 ? 0x1c0u : k < 6 ? 0x1ffu : 0x007u;
-      const uint32_t zc = k % 3 == 0 ? 0x124u : k % 3 == 1 ? 0x1ffu : 0x049u;
-      act |= ((st[k] >> 1) & zr & zc) != 0u;
-    }
-    if (!act && threadIdx.x < 64) stg(iter_state(f, it), t, st[4] & 1u);
-  }
-  return __ballot(act);
-}
 
 // The iteration on one tile, by kIterThreads threads; every barrier is
 // block-uniform.
 template <int TH, int TW_>
-__device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, SmemIter<TH, TW_>& s) {
+__device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, const IterList& next,
+                                          SmemIter<TH, TW_>& s) {
   using SM = SmemIter<TH, TW_>;
   constexpr int NT = kIterThreads, RH = SM::RH, RW = SM::RW, QR = SM::QR, QC = SM::QC, NW = SM::NW;
   constexpr int HL = kIterHalo, QCAP = SM::kQuadCap, ICAP = SM::kItemCap;
@@ -505,9 +488,11 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, S
   const int ry0 = y0 - HL, rx0 = x0 - HL;
   uint32_t st[9];  // planes of the 3x3 tiles after the previous iteration
   if (it > 0) {
-    const uint32_t v = grid.state(iter_state(f, it - 1), ty, tx, lane < 9 ? lane : 4);
+    const int n = grid.neighbour(ty, tx, lane < 9 ? lane : 4);
+    const uint32_t v = __hip_atomic_load(gp(iter_state(f) + max(n, 0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t p = (v & 1u) ^ ((v >> 1) == (uint32_t)(it + 1) ? 1u : 0u);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) st[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k) & 1u;
+    for (int k = 0; k < 9; ++k) st[k] = (uint32_t)__builtin_amdgcn_readlane((int)p, k);
   }
   const uint32_t plane = it > 0 ? st[4] : 1u;  // this iteration writes plane ^ 1
   const bool inner = ry0 >= 0 && rx0 >= 0 && ry0 + RH <= h && rx0 + RW <= w;
@@ -554,13 +539,11 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, S
     if (mq == NW - 1) mword = (uint32_t)(cw >> (TW_ - 8)) | ((uint32_t)(word(sr, tx + 1) & 0xffull) << 8);
     if (NW == 3 && mq == 1) mword = (uint32_t)(cw >> 24);
   }
-  if (inner) {
-    // C4 threads per row of 16-byte groups, RP rows at a time
+  {
+    // C4 threads per row of 4 pixels each, RP rows at a time
     constexpr int C4 = RW / 4, RP = NT / C4, K = (RH + RP - 1) / RP;
     typedef uint16_t h4u __attribute__((ext_vector_type(4), aligned(2)));
     const int r0 = tid / C4, q0 = 4 * (tid - r0 * C4);
-    const uint32_t o0 = (uint32_t)(r0 * w + q0), step = (uint32_t)(RP * w);  // from the region's corner
-    const int64_t corner = (int64_t)ry0 * w + rx0;
     auto put = [&](int k, float a, float b, float c, float d) __attribute__((always_inline)) {
       const int r = r0 + k * RP;
       if (RP * C4 != NT && r0 >= RP) return;
@@ -573,34 +556,41 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, S
       mx = vmax3_abs(vmax3_abs(mx, a, b), c, d);
       *reinterpret_cast<float4*>(&s.c[r][q0]) = float4{a, b, c, d};
     };
-    // (threads and rows past the region load its last row again)
-    auto at = [&](int k) __attribute__((always_inline)) -> uint32_t {
-      return (r0 + k * RP < RH) ? o0 + (uint32_t)k * step : o0;
-    };
-    if (src16) {
-      const uint16_t* base = src16 + corner;
-      h4u v[K];
+    if (inner) {
+      const uint32_t o0 = (uint32_t)(r0 * w + q0), step = (uint32_t)(RP * w);  // from the region's corner
+      const int64_t corner = (int64_t)ry0 * w + rx0;
+      // (threads and rows past the region load its first rows again)
+      auto at = [&](int k) __attribute__((always_inline)) -> uint32_t {
+        return (r0 + k * RP < RH) ? o0 + (uint32_t)k * step : o0;
+      };
+      if (src16) {
+        const uint16_t* base = src16 + corner;
+        h4u v[K];
 #pragma unroll
-      for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) h4u*)(base + at(k));
+        for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) h4u*)(base + at(k));
 #pragma unroll
-      for (int k = 0; k < K; ++k) put(k, (float)v[k].x, (float)v[k].y, (float)v[k].z, (float)v[k].w);
-    } else {
-      const float* base = src + corner;
-      f4u v[K];
+        for (int k = 0; k < K; ++k) put(k, (float)v[k].x, (float)v[k].y, (float)v[k].z, (float)v[k].w);
+      } else {
+        const float* base = src + corner;
+        f4u v[K];
 #pragma unroll
-      for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) f4u*)(base + at(k));
+        for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) f4u*)(base + at(k));
 #pragma unroll
-      for (int k = 0; k < K; ++k) put(k, v[k].x, v[k].y, v[k].z, v[k].w);
-    }
-  } else {
-#pragma unroll 4
-    for (int i = tid; i < RH * RW; i += NT) {
-      const int r = i / RW, q = i - r * RW;
-      const int64_t gi = (int64_t)clampi(ry0 + r, h - 1) * w + clampi(rx0 + q, w - 1);
-      const float v = (src16 ? (float)ldg(src16, gi) : ldg(src, gi)) + 0.0f;
-      mn = vmin(mn, v);
-      mx = vmax3_abs(mx, v, v);
-      s.c[r][q] = v;
+        for (int k = 0; k < K; ++k) put(k, v[k].x, v[k].y, v[k].z, v[k].w);
+      }
+    } else {  // clamped on the frame, pixel by pixel
+      int cx[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) cx[b] = clampi(rx0 + q0 + b, w - 1);
+      float v[K][4];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const int64_t row = (int64_t)clampi(ry0 + min(r0 + k * RP, RH - 1), h - 1) * w;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) v[k][b] = src16 ? (float)ldg(src16, row + cx[b]) : ldg(src, row + cx[b]);
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k) put(k, v[k][0], v[k][1], v[k][2], v[k][3]);
     }
   }
   if (!inner)  // edge tiles read blocks no one lists (and drop what they hold)
@@ -930,7 +920,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, S
           const uint32_t z = ((redo & col_bits(ww, HL, 2 * HL)) ? 1u : 0u) |
                              ((redo & col_bits(ww, 2 * HL, TW_)) ? 2u : 0u) |
                              ((redo & col_bits(ww, TW_, TW_ + HL)) ? 4u : 0u);
-          atomicOr(&s.zones, z << (1 + 3 * zy));
+          atomicOr(&s.zones, z << (3 * zy));
         }
       }
     }
@@ -1028,8 +1018,28 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, S
   // ---- state, mask bits, and in iteration 0 the whole tile's outputs
   const bool write = changed || it == 0;
   next_phase();
-  if (tid == 0) stg(iter_state(f, it), tile, write ? ((plane ^ 1u) | (changed ? s.zones : 0u)) : plane);
   if (!write) return;
+  if (tid == 0) {
+    __hip_atomic_store(gp(iter_state(f) + tile), ((uint32_t)(it + 1) << 1) | (plane ^ 1u), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    if (it == 0) {
+      stg(iter_stamp(f, 0), tile, 0u);
+      stg(iter_stamp(f, 1), tile, 0u);
+    }
+  }
+  if (it > 0 && it + 1 < f.niter && tid < 9) {
+    // the tiles whose region holds a change: this one, and those beside a
+    // zone along its edge that holds one
+    const uint32_t zr = tid < 3 ? 0x007u : tid < 6 ? 0x1ffu : 0x1c0u;
+    const uint32_t zc = tid % 3 == 0 ? 0x049u : tid % 3 == 1 ? 0x1ffu : 0x124u;
+    const int n = grid.neighbour(ty, tx, tid);
+    if (n >= 0 && (s.zones & zr & zc)) {
+      const uint32_t stamp = (uint32_t)(it + 2);
+      if (__hip_atomic_exchange(gp(iter_stamp(f, it + 1) + n), stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) !=
+              stamp && next.list)
+        stg(next.list, atom_add(next.count, 1u), next.base + n);
+    }
+  }
   if (tid < TH && y0 + tid < h) {
     const uint32_t* m = &s.word(kBitM, tid + HL, 0);
     uint64_t word = (m[0] >> 8) | (m[1] << 24);
@@ -1073,20 +1083,10 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, S
   }
 }
 
-// A block's share of iteration it: n tiles from t0 on.
-template <int TH, int TW_>
-__device__ __forceinline__ void tiles_iter(const FrameDev& f, int it, int t0, int n, SmemIter<TH, TW_>& s) {
-  if (stopped(f, it)) return;  // the outputs already hold the result
-  unsigned long long act = n >= 64 ? ~0ull : (1ull << n) - 1ull;
-  // a new gain changes the noise model everywhere
-  if (it > 0 && !f.est_gain) act = iter_active<TH, TW_>(f, it, t0, n);
-#pragma unroll 1
-  while (act) {
-    const int k = __ffsll((long long)act) - 1;
-    act &= act - 1;
-    tile_iter<TH, TW_>(f, it, t0 + k, s);
-    if (act) __syncthreads();  // the next tile reuses the LDS
-  }
+// Whether iteration it has work for a tile (of one block per tile launches).
+// A new gain changes the noise model everywhere.
+__device__ __forceinline__ bool iter_due(const FrameDev& f, int it, int tile) {
+  return it <= 1 || f.est_gain || ldg(iter_stamp(f, it), tile) == (uint32_t)(it + 1);
 }
 
 }  // namespace lac

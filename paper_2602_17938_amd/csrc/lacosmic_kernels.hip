@@ -104,15 +104,29 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused(const FrameDev* __restr
   tile_fused<kFusedThreads>(f, it, xcd_remap(blockIdx.x, gridDim.x), s);
 }
 
-// One whole iteration of a frame, `chunk` consecutive TH x TW_ output tiles
-// per block (consecutive blocks on one XCD: their regions overlap).
+// One whole iteration of a frame on TH x TW_ output tiles: every tile, one
+// block each (consecutive tiles on one XCD: their regions overlap), or with
+// `listed` those the previous iteration listed, shared out over the grid.
 template <int TH, int TW_>
 __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter(const FrameDev* __restrict__ fp, int it,
-                                                          int ntiles, int chunk) {
+                                                                   bool listed) {
   __shared__ SmemIter<TH, TW_> s;
   const FrameDev f = *fp;
-  const int t0 = xcd_remap(blockIdx.x, gridDim.x) * chunk;
-  tiles_iter<TH, TW_>(f, it, t0, min(chunk, ntiles - t0), s);
+  if (stopped(f, it)) return;  // the outputs already hold the result
+  // the lists alternate between two planes no one-launch iteration uses
+  const IterList next{reinterpret_cast<int*>((it & 1) ? f.splane : f.sp), f.counts + it + 1, 0};
+  if (!listed) {
+    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    if (iter_due(f, it, t)) tile_iter<TH, TW_>(f, it, t, next, s);
+    return;
+  }
+  const int* list = reinterpret_cast<const int*>((it & 1) ? f.sp : f.splane);
+  const unsigned int n = ldg(f.counts, it);
+#pragma unroll 1
+  for (unsigned int i = blockIdx.x; i < n; i += gridDim.x) {
+    tile_iter<TH, TW_>(f, it, __builtin_amdgcn_readfirstlane(ldg(list, i)), next, s);
+    __syncthreads();  // the next tile reuses the LDS
+  }
 }
 
 // Index of the last frame whose first tile is at or before tile t (base: the
@@ -133,26 +147,27 @@ __device__ __forceinline__ int frame_of_wave(const int* base, int nframes, int t
 }
 
 // The same over the tiles of many frames (tile_base: prefix sums of their
-// TH x TW_ tile counts).  it < 0: each frame runs its own FrameDev::it.
+// TH x TW_ tile counts).  it < 0: each frame runs its own FrameDev::it (and
+// no list is kept).  lists: two lists of as many entries as there are tiles,
+// used in turn; counts: their lengths by iteration (cleared before the run).
 template <int TH, int TW_>
-__global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(const FrameDev* __restrict__ frames,
-                                                                 const int* tile_base, int nframes, int it,
-                                                                 int chunk) {
+__global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(
+    const FrameDev* __restrict__ frames, const int* tile_base, int nframes, int it, bool listed, int* lists,
+    unsigned int* counts) {
   __shared__ SmemIter<TH, TW_> s;
   const int total = ldg(tile_base, nframes);
-  int t = xcd_remap(blockIdx.x, gridDim.x) * chunk;
-  const int t1 = min(t + chunk, total);
-  int fi = frame_of_wave(tile_base, nframes, t);
+  const int* list = lists + (int64_t)(it & 1) * total;
+  const unsigned int n = listed ? ldg(counts, it) : gridDim.x;
 #pragma unroll 1
-  while (t < t1) {  // a run of tiles of one frame at a time
+  for (unsigned int i = blockIdx.x; i < n; i += gridDim.x) {
+    const int t = listed ? __builtin_amdgcn_readfirstlane(ldg(list, i)) : xcd_remap(i, gridDim.x);
+    const int fi = frame_of_wave(tile_base, nframes, t);
     const int b0 = __builtin_amdgcn_readfirstlane(ldg(tile_base, fi));
-    const int b1 = __builtin_amdgcn_readfirstlane(ldg(tile_base, fi + 1));
     const FrameDev f = frames[fi];
-    const int n = min(t1, b1) - t;
-    tiles_iter<TH, TW_>(f, it >= 0 ? it : f.it, t - b0, n, s);
-    t += n;
-    ++fi;
-    if (t < t1) __syncthreads();
+    const int fit = it >= 0 ? it : f.it;
+    const IterList next{it >= 0 ? lists + (int64_t)((it + 1) & 1) * total : nullptr, counts + it + 1, b0};
+    if (!stopped(f, fit) && (listed || iter_due(f, fit, t - b0))) tile_iter<TH, TW_>(f, fit, t - b0, next, s);
+    if (listed) __syncthreads();  // the next tile reuses the LDS
   }
 }
 
@@ -469,15 +484,16 @@ static void sparse_launch(const FrameDev* fd, int it, unsigned ns, hipStream_t s
   k_sparse_frame<WHICH><<<ns, 256, 0, st>>>(fd, it);
 }
 
-// Tiles per block of a one-launch iteration.  Iteration 0 works on every
-// tile, iteration 1 on nearly every one (most hold a pixel that iteration 0
-// changed): one block each, scheduled as they finish.  Later ones skip most
-// tiles, and a block that only finds that out still takes its turn on a CU
-// (three fit at once): up to 8 tiles per block, looked at side by side, but
-// at least two blocks per CU slot.
-static int iter_chunk(int tiles, int it) {
-  if (it <= 1) return 1;
-  return std::max(1, std::min(8, tiles / (6 * (sparse_blocks() / 8))));
+// Blocks of a one-launch iteration of `tiles` tiles: from iteration 2 on most
+// tiles are skipped, and only the listed ones are run, by as many blocks as
+// the CUs hold at once (four each).  Iterations 0 and 1 and those of frames
+// that estimate their gain (all) run one block per tile.  (Every block that
+// only finds its tile not due costs several memory round trips: the launches
+// of iterations 2 and 3 on a 6400 x 9600 frame, 650 of 15000 tiles due and
+// then none, took 81 us scanning 7 tiles per block and take 48 with the list.)
+static bool iter_listed(int it, bool all) { return it >= 2 && !all; }
+static int iter_blocks(int tiles, bool listed) {
+  return listed ? std::min(tiles, 4 * (sparse_blocks() / 8)) : tiles;
 }
 
 // One iteration: grid sizes from the host copy f, the kernels read the
@@ -498,13 +514,12 @@ static hipError_t frame_iter_t(const FrameDev& f, const FrameDev* fd, int it, hi
     }
     if (f.fused == kFusedTiles) {
       const int shape = iter_shape(px);
-      const int nt = (int)iter_tiles(f.h, f.w, shape);
-      const int chunk = f.est_gain ? 1 : iter_chunk(nt, it);
-      const unsigned nb = (unsigned)((nt + chunk - 1) / chunk);
+      const bool listed = iter_listed(it, f.est_gain != 0);
+      const unsigned nb2 = (unsigned)iter_blocks((int)iter_tiles(f.h, f.w, shape), listed);
       if (shape == kIterSmall)
-        k_iter<32, 32><<<nb, kIterThreads, 0, st>>>(fd, it, nt, chunk);
+        k_iter<32, 32><<<nb2, kIterThreads, 0, st>>>(fd, it, listed);
       else
-        k_iter<64, 64><<<nb, kIterThreads, 0, st>>>(fd, it, nt, chunk);
+        k_iter<64, 64><<<nb2, kIterThreads, 0, st>>>(fd, it, listed);
       return hipGetLastError();
     }
     const unsigned nt = (unsigned)(((f.h + FT - 1) / FT) * ((f.w + FT - 1) / FT));
@@ -649,14 +664,16 @@ int64_t iter_tiles(int64_t h, int64_t w, int shape) {
   return ((h + e - 1) / e) * ((w + e - 1) / e);
 }
 
-hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, hipStream_t st) {
+hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, bool all, hipStream_t st) {
   if (a.blocks <= 0) return hipSuccess;
-  const int chunk = iter_chunk(a.blocks, it);
-  const unsigned nb = (unsigned)((a.blocks + chunk - 1) / chunk);
+  const bool listed = it >= 0 && iter_listed(it, all);
+  const unsigned nb = (unsigned)iter_blocks(a.blocks, listed);
   if (shape == kIterSmall)
-    k_iter_frames<32, 32><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, chunk);
+    k_iter_frames<32, 32><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, listed, a.lists,
+                                                       a.cursors);
   else
-    k_iter_frames<64, 64><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, chunk);
+    k_iter_frames<64, 64><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, listed, a.lists,
+                                                       a.cursors);
   return hipGetLastError();
 }
 

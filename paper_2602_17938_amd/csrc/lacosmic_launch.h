@@ -105,6 +105,7 @@ struct QueueArgs {
   unsigned int* cursors;
   int cursor_slot;
   int blocks;  // persistent grid size (queue mode) or the pass's tile count (grid mode)
+  int* lists = nullptr;  // one-launch iterations: two tile lists (cursors: their lengths)
 };
 
 // Zero the cursors [0, ncursors) and, if zero_counters, every frame's
@@ -117,8 +118,11 @@ hipError_t launch_queue_init(const QueueArgs& a, int ncursors, int zero_counters
 hipError_t launch_queue_pass(const QueueArgs& a, int pass, int it, int cfg, int mode,
                              hipStream_t st);
 // One iteration of every frame of a table in one launch (lacosmic_iter.h):
-// a.tile_base and a.blocks count the shape's tiles; it as above.
-hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, hipStream_t st);
+// a.tile_base and a.blocks count the shape's tiles, a.lists has room for two
+// lists of them and a.cursors, cleared before the run, niter + 1 lengths (both
+// unused with it < 0); it as above.  all: every tile has work (some frame
+// estimates its gain).
+hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, bool all, hipStream_t st);
 // Gain estimate of iteration it (it < 0: each frame's own FrameDev::it) for
 // the frames of a table (one frame: its record) that estimate their gain:
 // a reset, then up to 5 sigma-clipping rounds of three passes and the final

@@ -42,8 +42,17 @@ struct NoiseCoef {
 struct GainWork {
   unsigned int hist[4096];          // histogram of the current selection pass
   unsigned long long acc[5][256];   // exact-sum accumulators by exponent
+  // exact sums of the values whose exponent lies in a window from ebase, in
+  // units of ebase's last place: signed sum, and the sum of squares as 32-bit
+  // digits (low, middle, high, each summed in 64 bits)
+  unsigned long long wide[4];
   uint32_t klo, khi;                // kept values: keys in [klo, khi]
   uint32_t prefix, rank;            // median search: key digits found, rank left
+  uint32_t near0;                   // first key of the near histogram (0: none this round)
+  int found;                        // the round's median came from it: no selection passes
+  unsigned long long below;         // kept values below near0
+  uint32_t kbin;                    // first of the bins counted in registers
+  int ebase;                        // first exponent of the window (1 or more)
   int round;                        // clipping rounds applied
   int done;                         // this iteration's estimate is final
   unsigned int blocks_done;         // blocks of the current pass that finished

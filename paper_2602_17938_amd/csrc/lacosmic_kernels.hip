@@ -410,7 +410,7 @@ __global__ void k_gain_reset(const FrameDev* __restrict__ frames, int it) {
   const FrameDev& f = frames[blockIdx.x];
   const int fit = it >= 0 ? it : f.it;
   if (!f.est_gain || stopped(f, fit)) return;
-  gain_reset(f);
+  gain_reset(f, fit);
 }
 
 template <int P>
@@ -431,8 +431,10 @@ __global__ void k_u16_to_f32(const uint16_t* in, float* out, int64_t n) {
 
 // ------------------------------------------------------------ launchers
 int gain_blocks(int64_t pixels) {
-  const int64_t want = (pixels + 16 * kGainThreads - 1) / (16 * kGainThreads);
-  return (int)std::min<int64_t>(1024, std::max<int64_t>(1, want));
+  // 32 pixels per thread (two rounds of loads), up to two blocks per CU (four:
+  // 4096^2 first passes 59 -> 62 us, more atomics on the few bins in use)
+  const int64_t want = (pixels + 32 * kGainThreads - 1) / (32 * kGainThreads);
+  return (int)std::min<int64_t>(512, std::max<int64_t>(1, want));
 }
 
 hipError_t launch_gain(const FrameDev* frames, int nframes, int it, int nbx, hipStream_t st) {

@@ -520,21 +520,27 @@ extern "C" int lacosmic_run_batch(int32_t n, const float* const* imgs, const int
       if (rc) return rc;
       if (p[i].flags & LACOSMIC_F_ESTIMATE_GAIN) est = 1;
     }
-    // outputs of one frame must not overlap any buffer of another
+    // outputs of one frame must not overlap any buffer of another: a sweep
+    // over all buffers by address (those of one frame do not overlap each
+    // other any more); inputs may overlap inputs
+    struct Range {
+      uintptr_t lo, hi;
+      bool out;
+    };
+    std::vector<Range> ranges;
+    ranges.reserve(3 * (size_t)n);
     for (int i = 0; i < n; ++i) {
-      const size_t ni = (size_t)hs[i] * (size_t)ws[i];
-      const uintptr_t oc = (uintptr_t)out_cleans[i], om = (uintptr_t)out_masks[i];
-      for (int j = 0; j < n; ++j) {
-        if (j == i) continue;
-        const size_t nj = (size_t)hs[j] * (size_t)ws[j];
-        const uintptr_t ranges[3][2] = {{(uintptr_t)imgs[j], (size_t)input_bytes(p[j]) * nj},
-                                        {(uintptr_t)out_cleans[j], 4 * nj},
-                                        {(uintptr_t)out_masks[j], nj}};
-        for (auto& r : ranges) {
-          if ((oc < r[0] + r[1] && r[0] < oc + 4 * ni) || (om < r[0] + r[1] && r[0] < om + ni))
-            return LACOSMIC_EALIAS;
-        }
-      }
+      const size_t px = (size_t)hs[i] * (size_t)ws[i];
+      const uintptr_t in = (uintptr_t)imgs[i], oc = (uintptr_t)out_cleans[i], om = (uintptr_t)out_masks[i];
+      ranges.push_back(Range{in, in + (size_t)input_bytes(p[i]) * px, false});
+      ranges.push_back(Range{oc, oc + 4 * px, true});
+      ranges.push_back(Range{om, om + px, true});
+    }
+    std::sort(ranges.begin(), ranges.end(), [](const Range& a, const Range& b) { return a.lo < b.lo; });
+    uintptr_t in_end = 0, out_end = 0;
+    for (const Range& r : ranges) {
+      if (r.lo < out_end || (r.out && r.lo < in_end)) return LACOSMIC_EALIAS;
+      (r.out ? out_end : in_end) = std::max(r.out ? out_end : in_end, r.hi);
     }
     const int niter = p[0].niter;
     const int early = (p[0].flags & LACOSMIC_F_EARLY_STOP) ? 1 : 0;

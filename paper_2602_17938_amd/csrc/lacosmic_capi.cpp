@@ -216,6 +216,7 @@ DevCtx* ctx_for(int dev) {
 }
 
 hipStream_t DevCtx::stream_after_null() {
+  if (hipStreamQuery(nullptr) == hipSuccess) return stream;  // nothing to wait for
   if (hipEventRecord(null_done, nullptr) != hipSuccess ||
       hipStreamWaitEvent(stream, null_done, 0) != hipSuccess)
     return nullptr;
@@ -320,24 +321,12 @@ void shutdown_all() {
   g_ctx.clear();
 }
 
-// Read back counters and status after the stream's work through the host
-// buffer pin (kStatsHostBytes); fill stats.
-int finish_with(char* pin, hipStream_t s, const FrameDev& f, lacosmic_stats* st) {
-  // the per-iteration counts and the unreplaced-pixel count after them, the
-  // status word, and the noise constants of the first 16 estimated gains
-  const size_t nbytes = sizeof(unsigned long long) * ((size_t)f.niter + 1);
+// Fills st from what a run reported: its niter + 1 counters, status word and
+// the noise constants of the first 16 estimated gains.
+static int report(const FrameDev& f, const char* counters, int status, const char* coef,
+                  lacosmic_stats* st) {
+  const unsigned long long* nn = reinterpret_cast<const unsigned long long*>(counters);
   const int ncoef = f.niter < 16 ? f.niter : 16;
-  const size_t coef_at = align256(nbytes + sizeof(int));
-  if (hipMemcpyAsync(pin, f.n_new, nbytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipMemcpyAsync(pin + nbytes, f.status, sizeof(int), hipMemcpyDeviceToHost, s) !=
-          hipSuccess ||
-      (f.est_gain && hipMemcpyAsync(pin + coef_at, f.coef, sizeof(NoiseCoef) * ncoef,
-                                    hipMemcpyDeviceToHost, s) != hipSuccess) ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return LACOSMIC_EHIP;
-  const unsigned long long* nn = reinterpret_cast<const unsigned long long*>(pin);
-  int status = 0;
-  std::memcpy(&status, pin + nbytes, sizeof(int));
   if (st) {
     std::memset(st, 0, sizeof(*st));
     int run = f.niter;
@@ -356,7 +345,7 @@ int finish_with(char* pin, hipStream_t s, const FrameDev& f, lacosmic_stats* st)
     for (int k = 0; k < ncoef; ++k) {
       if (f.est_gain) {
         NoiseCoef nc;
-        std::memcpy(&nc, pin + coef_at + sizeof(NoiseCoef) * k, sizeof(nc));
+        std::memcpy(&nc, coef + sizeof(NoiseCoef) * k, sizeof(nc));
         st->gain[k] = k < run ? nc.gain : 0.0f;
         st->gain_estimated[k] = k < run ? (int8_t)(nc.valid ? 1 : -1) : (int8_t)0;
       } else {
@@ -367,8 +356,34 @@ int finish_with(char* pin, hipStream_t s, const FrameDev& f, lacosmic_stats* st)
   return (status & 1) ? LACOSMIC_ENONFINITE : LACOSMIC_OK;
 }
 
-int finish_sync(DevCtx* c, hipStream_t s, const FrameDev& f, lacosmic_stats* st) {
-  return finish_with(static_cast<char*>(c->pinned), s, f, st);
+int finish_with(char* pin, hipStream_t s, const FrameDev& f, lacosmic_stats* st) {
+  // one copy from the counters to the status word
+  const size_t nbytes = (size_t)(reinterpret_cast<const char*>(f.status) -
+                                 reinterpret_cast<const char*>(f.n_new)) + sizeof(int);
+  const int ncoef = f.niter < 16 ? f.niter : 16;
+  const size_t coef_at = align256(nbytes);
+  if (coef_at + sizeof(NoiseCoef) * ncoef > kStatsHostBytes) return LACOSMIC_EHIP;
+  if (hipMemcpyAsync(pin, f.n_new, nbytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
+      (f.est_gain && hipMemcpyAsync(pin + coef_at, f.coef, sizeof(NoiseCoef) * ncoef,
+                                    hipMemcpyDeviceToHost, s) != hipSuccess) ||
+      hipStreamSynchronize(s) != hipSuccess)
+    return LACOSMIC_EHIP;
+  int status = 0;
+  std::memcpy(&status, pin + nbytes - sizeof(int), sizeof(int));
+  return report(f, pin, status, pin + coef_at, st);
+}
+
+int finish_sync(DevCtx* c, hipStream_t s, const FrameDev& f, const FrameDev* fd, lacosmic_stats* st) {
+  char* pin = static_cast<char*>(c->pinned);
+  const size_t nbytes = sizeof(unsigned long long) * ((size_t)f.niter + 1);
+  const size_t coef_at = align256(nbytes + sizeof(int));
+  const int ncoef = f.est_gain ? (f.niter < 16 ? f.niter : 16) : 0;
+  if (launch_report(fd, pin, (int)coef_at, ncoef, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
+    return LACOSMIC_EHIP;
+  int status = 0;
+  std::memcpy(&status, pin + nbytes, sizeof(int));
+  return report(f, pin, status, pin + coef_at, st);
 }
 
 }  // namespace lac
@@ -417,26 +432,27 @@ int lacosmic_run_ex(const float* img, int64_t h, int64_t w, const lacosmic_param
     if (!ws) {
       rc = c->ensure_ws(L.total);
       if (rc) return rc;
-      if (hipStreamWaitEvent(s, c->ws_done, 0) != hipSuccess) return LACOSMIC_EHIP;
+      // (a caller's stream may be capturing, where an event may not be queried)
+      if ((hip_stream || hipEventQuery(c->ws_done) != hipSuccess) &&
+          hipStreamWaitEvent(s, c->ws_done, 0) != hipSuccess)
+        return LACOSMIC_EHIP;
       ws = static_cast<char*>(c->ws);
     }
     FrameDev f = make_frame(img, h, w, *p, out_mask, out_clean, ws, L, c->cfg);
     f.fused = fused_form(h, w, *p, workspace != nullptr);
     FrameDev* fd = reinterpret_cast<FrameDev*>(ws + L.rec);
-    if (launch_put_frame(f, fd, s) != hipSuccess) return LACOSMIC_EHIP;
     if (c->use_graphs) {  // the recorded run for this workspace and shape
+      if (launch_put_frame(f, fd, s) != hipSuccess) return LACOSMIC_EHIP;
       FrameGraph* g = c->frame_graph(f, fd, ws, L.nstamps, c->cfg);
       if (!g || hipGraphLaunch(g->exec, s) != hipSuccess || hipEventRecord(g->done, s) != hipSuccess)
         return LACOSMIC_EHIP;
     } else {
-      if (launch_init(f.n_new, f.niter, f.status, f.counts, f.b1s, (int64_t)L.nstamps, s) !=
-          hipSuccess)
-        return LACOSMIC_EHIP;
+      if (launch_begin(f, fd, (int64_t)L.nstamps, s) != hipSuccess) return LACOSMIC_EHIP;
       for (int it = 0; it < f.niter; ++it)
         if (launch_iteration(f, fd, it, c->cfg, s) != hipSuccess) return LACOSMIC_EHIP;
     }
     if (!workspace && hipEventRecord(c->ws_done, s) != hipSuccess) return LACOSMIC_EHIP;
-    if (hip_stream == nullptr || st != nullptr) return finish_sync(c, s, f, st);
+    if (hip_stream == nullptr || st != nullptr) return finish_sync(c, s, f, fd, st);
     return LACOSMIC_OK;
   });
 }

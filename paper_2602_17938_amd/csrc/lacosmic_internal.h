@@ -110,10 +110,15 @@ struct DevCtx {
 
 DevCtx* ctx_for(int dev);
 void shutdown_all();
-int finish_sync(DevCtx* c, hipStream_t s, const FrameDev& f, lacosmic_stats* st);
-// Host bytes finish_with reads back through: niter + 1 counters, the status
-// word and 16 noise constants.
-constexpr size_t kStatsHostBytes = 8 * (kMaxIter + 1) + 256 + 16 * sizeof(NoiseCoef) + 256;
+// Both wait for the run's work and fill st (if not null).  finish_sync has a
+// launch write the results to the context's pinned buffer (a copy of each
+// part took about 10 us, the launch 3); finish_with copies them to host memory
+// of any kind.
+int finish_sync(DevCtx* c, hipStream_t s, const FrameDev& f, const FrameDev* fd, lacosmic_stats* st);
+// Host bytes finish_with reads back through: niter + 1 counters up to the
+// status word (which the layout puts after room for kMaxIter + 1) and 16 noise
+// constants.
+constexpr size_t kStatsHostBytes = 8 * (kMaxIter + 1) + 512 + 16 * sizeof(NoiseCoef) + 256;
 static_assert(kStatsHostBytes <= kPinnedBytes, "the context's pinned buffer holds the stats");
 int finish_with(char* host, hipStream_t s, const FrameDev& f, lacosmic_stats* st);
 

@@ -171,22 +171,42 @@ __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(
   }
 }
 
-// Stores a frame record (a kernel argument) in device memory.
-__global__ void k_put_frame(FrameDev f, FrameDev* dst) {
+__device__ __forceinline__ void put_frame(const FrameDev& f, FrameDev* dst) {
   static_assert(sizeof(FrameDev) % 4 == 0, "the record is copied in 32-bit words");
   constexpr int kWords = (int)(sizeof(FrameDev) / 4);
   const uint32_t* src = reinterpret_cast<const uint32_t*>(&f);
   for (int i = threadIdx.x; i < kWords; i += blockDim.x) reinterpret_cast<uint32_t*>(dst)[i] = src[i];
 }
-
 // Zero one frame's per-iteration counters (and the unreplaced-pixel count
-// after them), list lengths and status.
-__global__ void k_init(unsigned long long* n_new, int niter, int* status, unsigned int* counts,
-                       int* stamps, int64_t nstamps) {
+// after them), list lengths, status and strip stamps.
+__device__ __forceinline__ void reset_counters(unsigned long long* n_new, int niter, int* status,
+                                               unsigned int* counts, int* stamps, int64_t nstamps) {
   for (int i = threadIdx.x; i <= niter; i += blockDim.x) n_new[i] = 0ull;
   for (int i = threadIdx.x; i < kCntPerIter * niter; i += blockDim.x) counts[i] = 0u;
   for (int64_t i = threadIdx.x; i < nstamps; i += blockDim.x) stamps[i] = 0;
   if (threadIdx.x == 0) *status = 0;
+}
+// Stores a frame record (a kernel argument) in device memory.
+__global__ void k_put_frame(FrameDev f, FrameDev* dst) { put_frame(f, dst); }
+__global__ void k_init(unsigned long long* n_new, int niter, int* status, unsigned int* counts,
+                       int* stamps, int64_t nstamps) {
+  reset_counters(n_new, niter, status, counts, stamps, nstamps);
+}
+// Both: the start of an eager single-frame run.
+__global__ void k_begin(FrameDev f, FrameDev* dst, int64_t nstamps) {
+  put_frame(f, dst);
+  reset_counters(f.n_new, f.niter, f.status, f.counts, f.b1s, nstamps);
+}
+
+// What a run reports, into host memory the kernel writes itself (pinned): the
+// niter + 1 counters, the status word after them, and at coef_at the noise
+// constants of the first ncoef estimated gains.
+__global__ void k_report(const FrameDev* __restrict__ fp, char* host, int coef_at, int ncoef) {
+  unsigned long long* ctr = reinterpret_cast<unsigned long long*>(host);
+  const int niter = fp->niter;
+  for (int i = threadIdx.x; i <= niter; i += blockDim.x) ctr[i] = fp->n_new[i];
+  if (threadIdx.x == 0) *reinterpret_cast<int*>(ctr + niter + 1) = *fp->status;
+  if (threadIdx.x < ncoef) reinterpret_cast<NoiseCoef*>(host + coef_at)[threadIdx.x] = fp->coef[threadIdx.x];
 }
 
 // ------------------------------------------------------------ tile queue
@@ -623,6 +643,16 @@ hipError_t launch_iteration(const FrameDev& f, const FrameDev* fd, int it, int c
     case 2: return frame_iter_t<8, 128>(f, fd, it, st);
     default: return frame_iter_t<16, 256>(f, fd, it, st);
   }
+}
+
+hipError_t launch_begin(const FrameDev& f, FrameDev* dst, int64_t nstamps, hipStream_t st) {
+  k_begin<<<1, 256, 0, st>>>(f, dst, f.fused == kFusedTiles ? 0 : nstamps);
+  return hipGetLastError();
+}
+
+hipError_t launch_report(const FrameDev* fd, char* host, int coef_at, int ncoef, hipStream_t st) {
+  k_report<<<1, 64, 0, st>>>(fd, host, coef_at, ncoef);
+  return hipGetLastError();
 }
 
 hipError_t launch_put_frame(const FrameDev& f, FrameDev* dst, hipStream_t st) {

@@ -82,6 +82,13 @@ hipError_t launch_init(unsigned long long* n_new, int niter, int* status, unsign
 // kernels read (launch_put_frame stores it).
 hipError_t launch_iteration(const FrameDev& f, const FrameDev* fd, int it, int cfg,
                             hipStream_t st);
+// The start of an eager single-frame run: launch_put_frame and launch_init in
+// one launch (the strip stamps only where the sparse passes use them).
+hipError_t launch_begin(const FrameDev& f, FrameDev* dst, int64_t nstamps, hipStream_t st);
+// Writes what the run of the frame at fd reports to pinned host memory: its
+// niter + 1 counters, the status word (an int) after them, ncoef noise
+// constants at coef_at.
+hipError_t launch_report(const FrameDev* fd, char* host, int coef_at, int ncoef, hipStream_t st);
 // Stores the frame record f at dst (device memory), in stream order.
 hipError_t launch_put_frame(const FrameDev& f, FrameDev* dst, hipStream_t st);
 // Queries the device properties the launchers use (once per process), so that

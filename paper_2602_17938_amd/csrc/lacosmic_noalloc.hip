@@ -69,10 +69,7 @@ extern "C" int lacosmic_run_noalloc(const float* img, int64_t h, int64_t w,
     FrameDev f = make_frame(img, h, w, *p, out_mask, out_clean, ws, L, kDefaultTileCfg);
     f.fused = fused_form(h, w, *p, false);
     FrameDev* fd = reinterpret_cast<FrameDev*>(ws + L.rec);
-    if (launch_put_frame(f, fd, s) != hipSuccess ||
-        launch_init(f.n_new, f.niter, f.status, f.counts, f.b1s, (int64_t)L.nstamps, s) !=
-            hipSuccess)
-      return LACOSMIC_EHIP;
+    if (launch_begin(f, fd, (int64_t)L.nstamps, s) != hipSuccess) return LACOSMIC_EHIP;
     for (int it = 0; it < f.niter; ++it)
       if (launch_iteration(f, fd, it, kDefaultTileCfg, s) != hipSuccess) return LACOSMIC_EHIP;
     if (hip_stream != nullptr && st == nullptr) return LACOSMIC_OK;

@@ -8,6 +8,7 @@ not built, importing this module raises ImportError -- there is no fallback.
 
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import re
@@ -135,6 +136,24 @@ def _dev_image(img, allow_u16=False):
     return img
 
 
+_SAME_DEVICE = contextlib.nullcontext()
+
+
+def _on(device):
+    """Context with `device` current (nothing to do where it is already)."""
+    if device.index == torch.cuda.current_device():
+        return _SAME_DEVICE
+    return torch.cuda.device(device)
+
+
+def _finish_current():
+    """Waits for torch's current stream, unless it is the legacy null stream,
+    after whose work the library stream orders itself."""
+    s = torch.cuda.current_stream()
+    if s.cuda_stream:
+        s.synchronize()
+
+
 def _typed(params: Params, img) -> Params:
     """params with the input-type flag set as the tensor's dtype says."""
     p = Params.from_buffer_copy(params)
@@ -162,9 +181,8 @@ def run(img, gain, readnoise, sigclip=4.5, sigfrac=0.3, objlim=5.0, niter=4):
     h, w = img.shape
     mask = torch.empty((h, w), dtype=torch.uint8, device=img.device)
     clean = torch.empty((h, w), dtype=torch.float32, device=img.device)
-    with torch.cuda.device(img.device):
-        # the library stream does not wait for torch's: finish pending work first
-        torch.cuda.current_stream().synchronize()
+    with _on(img.device):
+        _finish_current()
         rc = _lib.lacosmic_run(img.data_ptr(), h, w, gain, readnoise, sigclip, sigfrac, objlim,
                                int(niter), mask.data_ptr(), clean.data_ptr())
     _check(rc, "lacosmic_run")
@@ -191,11 +209,11 @@ def run_ex(img, params: Params, out_mask=None, out_clean=None, workspace=None,
             raise ValueError("workspace holds fewer than lacosmic_workspace_bytes(h, w) bytes")
         ws_ptr = workspace.data_ptr()
     st = Stats() if stats else None
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         if stream == "current":
             stream = torch.cuda.current_stream()
         elif stream is None:
-            torch.cuda.current_stream().synchronize()
+            _finish_current()
         s_ptr = None if stream is None else stream.cuda_stream
         rc = _lib.lacosmic_run_ex(img.data_ptr(), h, w, ctypes.byref(params), out_mask.data_ptr(),
                                   out_clean.data_ptr(), ws_ptr, s_ptr,
@@ -217,7 +235,7 @@ def run_noalloc(img, params: Params, out_mask=None, out_clean=None, stream="curr
     if out_clean is None:
         out_clean = torch.empty((h, w), dtype=torch.float32, device=img.device)
     st = Stats() if stats else None
-    with torch.cuda.device(img.device):
+    with _on(img.device):
         if stream == "current":
             stream = torch.cuda.current_stream()
         s_ptr = None if stream is None else stream.cuda_stream
@@ -262,30 +280,37 @@ def run_batch(imgs, params, out_masks=None, out_cleans=None, stream="current"):
     imgs = [_dev_image(x, allow_u16=True) for x in imgs]
     if isinstance(params, Params):
         params = [params] * n
-    params = [_typed(p, x) for p, x in zip(params, imgs)]
     if out_masks is None:
         out_masks = [torch.empty(x.shape, dtype=torch.uint8, device=x.device) for x in imgs]
     if out_cleans is None:
         out_cleans = [torch.empty(x.shape, dtype=torch.float32, device=x.device) for x in imgs]
-    VP = ctypes.c_void_p * n
-    I64 = ctypes.c_int64 * n
-    PA = Params * n
-    a_img = VP(*[x.data_ptr() for x in imgs])
-    a_h = I64(*[x.shape[0] for x in imgs])
-    a_w = I64(*[x.shape[1] for x in imgs])
-    a_p = PA(*params)
-    a_m = VP(*[m.data_ptr() for m in out_masks])
-    a_c = VP(*[c.data_ptr() for c in out_cleans])
-    with torch.cuda.device(imgs[0].device if n else torch.device("cuda")):
+    # one array of each kind, filled in bulk
+    def addresses(ts):
+        if len(ts) > n:
+            raise IndexError("more outputs than images")
+        return [t.data_ptr() for t in ts] + [0] * (n - len(ts))
+
+    ptrs = np.array(addresses(imgs) + addresses(out_masks) + addresses(out_cleans), np.uint64)
+    dims = np.array([x.shape for x in imgs], np.int64).reshape(n, 2).T.copy()
+    a_p = (Params * n)(*params[:n])  # copies: the callers' parameters stay as they are
+    for q, x in zip(a_p, imgs):
+        if x.dtype == torch.uint16:
+            q.flags |= F_INPUT_U16
+        elif q.flags & F_INPUT_U16:
+            q.flags &= ~F_INPUT_U16
+    VP, I64 = ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_int64)
+    at = ptrs.ctypes.data
+    with _on(imgs[0].device) if n else torch.cuda.device(torch.device("cuda")):
         if stream == "current":
             stream = torch.cuda.current_stream()
         elif stream is None:
-            torch.cuda.current_stream().synchronize()
+            _finish_current()
         s_ptr = None if stream is None else stream.cuda_stream
-        rc = _lib.lacosmic_run_batch(n, ctypes.cast(a_img, ctypes.POINTER(ctypes.c_void_p)),
-                                     a_h, a_w, a_p,
-                                     ctypes.cast(a_m, ctypes.POINTER(ctypes.c_void_p)),
-                                     ctypes.cast(a_c, ctypes.POINTER(ctypes.c_void_p)), s_ptr)
+        rc = _lib.lacosmic_run_batch(n, ctypes.cast(at, VP),
+                                     ctypes.cast(dims.ctypes.data, I64),
+                                     ctypes.cast(dims.ctypes.data + 8 * n, I64), a_p,
+                                     ctypes.cast(at + 8 * n, VP), ctypes.cast(at + 16 * n, VP),
+                                     s_ptr)
     _check(rc, "lacosmic_run_batch")
     return out_masks, out_cleans
 

@@ -156,6 +156,39 @@ __device__ __forceinline__ void wave_min_max(float& mn, float& mx) {
   dpp_step<0x142, 0xa>(mn, mx);  // row_bcast:15, 31
   dpp_step<0x143, 0xc>(mn, mx);
 }
+// Sums over the lanes up to each one.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15, 31
+  return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+}
+// n places each from a counter in LDS, by a whole wave: one atomic.  (An
+// atomicAdd of different amounts is a loop over the lanes, 40 cycles each: the
+// lists waited up to 2000 cycles on it.)
+__device__ __forceinline__ unsigned int wave_reserve(unsigned int* counter, unsigned int n) {
+  const unsigned int upto = (unsigned int)wave_scan((int)n);
+  const unsigned int total = (unsigned int)__builtin_amdgcn_readlane((int)upto, 63);
+  unsigned int base = 0u;
+  if (total) {  // (uniform)
+    if ((threadIdx.x & 63) == 0) base = atomicAdd(counter, total);
+    base = (unsigned int)__builtin_amdgcn_readfirstlane((int)base);
+  }
+  return base + upto - n;
+}
+// The OR over a wave.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  int x = (int)v;
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // as wave_scan
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return (uint32_t)__builtin_amdgcn_readlane(x, 63);
+}
 // Keys of n staged values: where the region holds no negative value (a
 // block-uniform choice) a value's bits are its key already.
 template <int N>
@@ -202,14 +235,14 @@ struct alignas(16) SmemIter {
   static constexpr int kQuadCap = TW_ == 64 ? 256 : QR * QC, kItemCap = TW_ == 64 ? 512 : 1024;
   typedef typename std::conditional<(kQuadCap <= 256), uint8_t, uint16_t>::type QIndex;
   float c[RH][RW];        // C_k at the clamped region coordinates
-  float s4[kQuadCap][4];  // S of the listed 2x2 blocks (before that, [0]: the block's position)
+  float s4[kQuadCap][4];  // S of the marked 2x2 blocks (before that: open candidates)
   uint32_t bits[kBitPlanes][kPlaneWords];
   uint64_t qbits[QR];      // the 2x2 blocks of the S area to evaluate, a bit row per block row
   uint16_t lst[kItemCap];  // items: region cell index
   QIndex qmap[QR * QC];    // a block's index in s4, by position
   float wmin[kIterThreads / 64], wmax[kIterThreads / 64];
   float mn, nmin, thr;  // the region's smallest value, the noise there, the candidates' bound
-  unsigned int cnt, nq, n2, fresh, unrep;
+  unsigned int cnt, nopen, n2, fresh, unrep;
   unsigned int zones;  // bit 3 zy + zx: 3x3 zones of the tile (8 pixels along the edges) with a change
   int any_b1, live;
   __device__ __forceinline__ static int at(int r, int ww) { return (r - BR0) * (NW + 1) + 1 + ww; }
@@ -245,35 +278,6 @@ struct alignas(16) SmemIter {
   }
 };
 
-// S at the four pixels of the 2x2 block whose top-left region cell is (y, x)
-// (even, at least 2 inside the region); cells outside the frame get values
-// nothing reads.
-template <typename SM>
-__device__ __forceinline__ void iter_quad(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
-                                          int x, bool nonneg, float* S) {
-  int v[36];
-#pragma unroll
-  for (int a = 0; a < 6; ++a)
-#pragma unroll
-    for (int b = 0; b < 6; ++b) v[a * 6 + b] = __float_as_int(s.c[y - 2 + a][x - 2 + b]);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = ((q >> 1) + 2) * 6 + (q & 1) + 2;
-    S[q] = lap_edge(__int_as_float(v[k]), __int_as_float(v[k - 6]), __int_as_float(v[k + 6]),
-                    __int_as_float(v[k - 1]), __int_as_float(v[k + 1]));
-  }
-  keys_of<36>(v, nonneg);
-  int m[4];
-  med25_block(v, m, f.sepmed);
-  if (noise_fast(nc)) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) S[q] = S[q] / (2.0f * noise_from_med<true>(m[q], nc, f.rn2));
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) S[q] = S[q] / (2.0f * noise_from_med<false>(m[q], nc, f.rn2));
-  }
-}
-
 // S (and N) at one region cell (2 or more inside the region).
 template <typename SM>
 __device__ __forceinline__ float iter_s(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
@@ -289,6 +293,58 @@ __device__ __forceinline__ float iter_s(const SM& s, const FrameDev& f, const No
   const int m = med25_of(v, f.sepmed);
   N = noise_fast(nc) ? noise_from_med<true>(m, nc, f.rn2) : noise_from_med<false>(m, nc, f.rn2);
   return L / (2.0f * N);
+}
+
+// Position of set bit n (from 0) of hi:lo.
+__device__ __forceinline__ int nth_bit(uint32_t lo, uint32_t hi, int n) {
+  const int c = __popc(lo);
+  int pos = n >= c ? 32 : 0;
+  uint32_t m = n >= c ? hi : lo;
+  n -= n >= c ? c : 0;
+#pragma unroll
+  for (int k = 16; k > 0; k >>= 1) {
+    const int below = __popc(m & ((1u << k) - 1u));
+    const bool up = n >= below;
+    n -= up ? below : 0;
+    m >>= up ? k : 0;
+    pos += up ? k : 0;
+  }
+  return pos;
+}
+
+// S at PX pixels from region cell (y, x) on (2 or more inside the region): the
+// pixel, it and the next of the row, or the 2x2 block; cells outside the frame
+// get values nothing reads.
+template <int PX, typename SM>
+__device__ __forceinline__ void iter_block(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
+                                           int x, bool nonneg, float* S) {
+  if (PX == 1) {
+    float N;
+    S[0] = iter_s(s, f, nc, y, x, nonneg, N);
+    return;
+  }
+  constexpr int ROWS = PX == 4 ? 6 : 5;
+  int v[36];
+#pragma unroll
+  for (int a = 0; a < 6; ++a)
+#pragma unroll
+    for (int b = 0; b < 6; ++b) v[a * 6 + b] = a < ROWS ? __float_as_int(s.c[y - 2 + a][x - 2 + b]) : 0;
+#pragma unroll
+  for (int q = 0; q < PX; ++q) {
+    const int k = ((q >> 1) + 2) * 6 + (q & 1) + 2;
+    S[q] = lap_edge(__int_as_float(v[k]), __int_as_float(v[k - 6]), __int_as_float(v[k + 6]),
+                    __int_as_float(v[k - 1]), __int_as_float(v[k + 1]));
+  }
+  keys_of<36>(v, nonneg);
+  int m[4];  // (with PX == 2 nothing uses the second row's, which are not formed)
+  med25_block(v, m, f.sepmed);
+  if (noise_fast(nc)) {
+#pragma unroll
+    for (int q = 0; q < PX; ++q) S[q] = S[q] / (2.0f * noise_from_med<true>(m[q], nc, f.rn2));
+  } else {
+#pragma unroll
+    for (int q = 0; q < PX; ++q) S[q] = S[q] / (2.0f * noise_from_med<false>(m[q], nc, f.rn2));
+  }
 }
 
 // On tiles at the frame's edge a window clamps on the frame: its rows and
@@ -365,95 +421,98 @@ __device__ __forceinline__ bool objlim_holds(const FrameDev& f, float m3, float 
   const float fn = (fr > 0.01f) ? fr : 0.01f;
   return (spv / fn) > f.objlim;
 }
-// Whether med7 of med3 at (y, x) is at most t, without forming any median: a
+// Whether med7 of med3 at (y, x) is at most t, without forming any median, by
+// the 4 lanes of a quad that share the arguments (all get the answer).  A
 // median is at most t when more than half its values are, so the 9x9 patch
-// becomes rows of bits [C <= t], the 3x3 majorities come from bit-sliced
-// sums of the three rows, and their number in the 7x7 window decides.  About
-// 390 operations, where the medians themselves take 1100.
+// becomes rows of bits [C <= t], the 3x3 majorities come from bit-sliced sums
+// of three rows, and their number in the 7x7 window decides.  Lane k forms
+// rows 2k to 2k + 2 of the patch and rows 2k and 2k + 1 of the majorities:
+// about 140 operations, where one lane alone took 390 (and the medians
+// themselves 1100) and the tile's other lanes waited for it.  A lane per row
+// took 90, but 16 lanes each: a bright star's 100 pixels needed 7 rounds.
 template <typename SM>
 __device__ __forceinline__ bool iter_med7_le(const SM& s, const FrameDev& f, int y, int x, int ry0,
                                              int rx0, bool inner, float t) {
-  uint32_t one[9], two[9];  // per row and column: the sum of 3 neighbours' bits
+  const int lane = threadIdx.x & 63, k2 = 2 * (lane & 3);
+  uint32_t one[4], two[4];  // per row and column: the sum of 3 neighbours' bits
 #pragma unroll
-  for (int a = 0; a < 9; ++a) {
+  for (int a = 0; a < 3; ++a) {
+    const float* p = &s.c[y - 4 + k2 + a][x - 4];
     uint32_t r = 0u;
 #pragma unroll
-    for (int b = 8; b >= 0; --b) r = r + r + (s.c[y - 4 + a][x - 4 + b] <= t ? 1u : 0u);
+    for (int b = 8; b >= 0; --b) r = r + r + (p[b] <= t ? 1u : 0u);
     const uint32_t r1 = r >> 1, r2 = r >> 2;
     one[a] = r ^ r1 ^ r2;
     two[a] = (r & r1) | (r & r2) | (r1 & r2);
   }
-  uint32_t le[7];  // [med3 <= t] of the 7x7 positions, bit b: column b
+  // row 2k + 3 is the next lane's second (quad_perm 1, 2, 3, 3; lane 3 has no
+  // use for it)
+  one[3] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)one[1], 0xf9, 0xf, 0xf, false);
+  two[3] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)two[1], 0xf9, 0xf, 0xf, false);
+  uint32_t le[2];  // [med3 <= t] of the 7 positions of rows k2, k2 + 1, bit b: column b
 #pragma unroll
-  for (int a = 0; a < 7; ++a) {
+  for (int a = 0; a < 2; ++a) {
     const uint32_t p0 = two[a], p1 = two[a + 1], p2 = two[a + 2];
     const uint32_t mj = (p0 & p1) | (p0 & p2) | (p1 & p2);
-    if (f.sepmed) {  // the median of the three row medians
-      le[a] = mj;
-      continue;
+    le[a] = mj;
+    if (!f.sepmed) {  // (separable: the median of the three row medians)
+      // 5 or more of 9: ones s1 + twos (p0 + p1 + p2 + c1) * 2
+      const uint32_t o0 = one[a], o1 = one[a + 1], o2 = one[a + 2];
+      const uint32_t s1 = o0 ^ o1 ^ o2, c1 = (o0 & o1) | (o0 & o2) | (o1 & o2);
+      const uint32_t px = p0 ^ p1 ^ p2, par = px ^ c1, car = px & c1;
+      le[a] = (mj & car) | ((mj ^ car) & (par | s1));
     }
-    // 5 or more of 9: ones s1 + twos (p0 + p1 + p2 + c1) * 2
-    const uint32_t o0 = one[a], o1 = one[a + 1], o2 = one[a + 2];
-    const uint32_t s1 = o0 ^ o1 ^ o2, c1 = (o0 & o1) | (o0 & o2) | (o1 & o2);
-    const uint32_t px = p0 ^ p1 ^ p2, par = px ^ c1, car = px & c1;
-    le[a] = (mj & car) | ((mj ^ car) & (par | s1));
   }
   if (!inner) {  // positions outside the frame take the nearest one inside
     const int gy = ry0 + y, gx = rx0 + x;
+    const int up = max(0, 3 - gy), dn = 6 - max(0, gy + 3 - (f.h - 1));
+    const uint32_t own0 = le[0], own1 = le[1];
 #pragma unroll
-    for (int a = 2; a >= 0; --a) {
-      le[a] = gy - 3 + a < 0 ? le[a + 1] : le[a];
-      le[6 - a] = gy + 3 - a >= f.h ? le[5 - a] : le[6 - a];
+    for (int a = 0; a < 2; ++a) {
+      const int row = min(max(k2 + a, up), dn), from = (lane & 60) + (row >> 1);
+      const uint32_t e = (uint32_t)__shfl((int)own0, from), o = (uint32_t)__shfl((int)own1, from);
+      le[a] = (row & 1) ? o : e;
     }
     const int lf = max(0, 3 - gx), rt = 6 - max(0, gx + 3 - (f.w - 1));  // first and last column inside
     const uint32_t lm = (1u << lf) - 1u, rm = 0x7fu & ~((2u << rt) - 1u);
 #pragma unroll
-    for (int a = 0; a < 7; ++a)
+    for (int a = 0; a < 2; ++a)
       le[a] = (le[a] & ~(lm | rm)) | (((le[a] >> lf) & 1u) ? lm : 0u) | (((le[a] >> rt) & 1u) ? rm : 0u);
   }
-  int n = 0;
-#pragma unroll
-  for (int a = 0; a < 7; ++a) {
-    const int k = __popc(le[a] & 0x7fu);
-    n += f.sepmed ? (k >= 4 ? 1 : 0) : k;
+  int n0 = __popc(le[0] & 0x7fu), n1 = k2 == 6 ? 0 : __popc(le[1] & 0x7fu);
+  if (f.sepmed) {
+    n0 = n0 >= 4 ? 1 : 0;
+    n1 = n1 >= 4 ? 1 : 0;
   }
+  int n = n0 + n1;
+  n += __builtin_amdgcn_update_dpp(0, n, 0xb1, 0xf, 0xf, false);  // quad_perm 1, 0, 3, 2
+  n += __builtin_amdgcn_update_dpp(0, n, 0x4e, 0xf, 0xf, false);  // quad_perm 2, 3, 0, 1
   return n >= (f.sepmed ? 4 : 25);
 }
 
-// The objlim test at region cell (y, x).
+// The objlim test at region cell (y, x) where the smallest med7 and N there
+// can be do not decide it: it holds unless med7 <= limit.
 template <typename SM>
-__device__ __forceinline__ bool iter_objlim(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
-                                            int x, int ry0, int rx0, bool inner, bool nonneg, float spv) {
-  const float m3 = iter_med3(s, f, y, x, nonneg);
-  if (objlim_holds(f, m3, s.mn, s.nmin, spv)) return true;  // for the smallest med7 and N there can be
+__device__ __forceinline__ float iter_objlim(const SM& s, const FrameDev& f, const NoiseCoef& nc, int y,
+                                             int x, bool nonneg, float m3, float spv) {
   float N;
   (void)iter_s(s, f, nc, y, x, nonneg, N);
-  // The largest med7 for which the test still fails (its value without
-  // rounding is m3 - d): then [med7 <= that] is the answer.
+  // the largest med7 for which the test still fails: its value without
+  // rounding is m3 - d
   const float d = N * (spv / f.objlim), t = m3 - d, e = (fabsf(m3) + d) * 0x1p-21f;
-  if (!objlim_holds(f, m3, t - e, N, spv) && objlim_holds(f, m3, t + e, N, spv)) {
-    uint32_t fails = gkey_of(t - e), holds = gkey_of(t + e);
+  // (or, where that overflows, anywhere among the floats)
+  const bool near = !objlim_holds(f, m3, t - e, N, spv) && objlim_holds(f, m3, t + e, N, spv);
+  if (!near && objlim_holds(f, m3, s.mn, N, spv)) return __int_as_float(0xff800000);
+  uint32_t fails = gkey_of(near ? t - e : s.mn), holds = near ? gkey_of(t + e) : 0xff800000u;
 #pragma unroll 1
-    while (holds - fails > 1u) {
-      const uint32_t mid = fails + ((holds - fails) >> 1);
-      if (objlim_holds(f, m3, gkey_float(mid), N, spv))
-        holds = mid;
-      else
-        fails = mid;
-    }
-    return !iter_med7_le(s, f, y, x, ry0, rx0, inner, gkey_float(fails));
-  }
-  // (an overflow above: bisect for med7 itself)
-  uint32_t lo = gkey_of(s.mn), hi = 0xff7fffffu;  // keys of the smallest value and the largest float
-#pragma unroll 1
-  while (lo < hi) {
-    const uint32_t mid = lo + ((hi - lo) >> 1);
-    if (iter_med7_le(s, f, y, x, ry0, rx0, inner, gkey_float(mid)))
-      hi = mid;
+  while (holds - fails > 1u) {
+    const uint32_t mid = fails + ((holds - fails) >> 1);
+    if (objlim_holds(f, m3, gkey_float(mid), N, spv))
+      holds = mid;
     else
-      lo = mid + 1u;
+      fails = mid;
   }
-  return objlim_holds(f, m3, gkey_float(lo), N, spv);
+  return gkey_float(fails);
 }
 
 // The tiles of a frame.
@@ -510,6 +569,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
   // ---- 1. stage C_k and M_k
   if (tid == 0) {
     s.cnt = 0u;
+    s.nopen = 0u;
     s.fresh = 0u;
     s.unrep = 0u;
     s.zones = 0u;
@@ -610,8 +670,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       return ldg((const float*)iter_values(f, p), (int64_t)(ry0 + r) * w + rx0 + q);
     };
     if (mr >= SM::BR0 && mr < SM::BR0 + SM::BROWS) s.word(kBitM, mr, mq) = mword;
-    const unsigned int nm = __popc(mword);
-    const unsigned int mbase = nm ? atomicAdd(&s.cnt, nm) : 0u;
+    const unsigned int mbase = wave_reserve(&s.cnt, (unsigned int)__popc(mword));
     __syncthreads();
     const unsigned int n = s.cnt;
     for (unsigned int c0 = 0; c0 < n; c0 += ICAP) {  // listed, then one thread each
@@ -666,55 +725,67 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       if (!(M <= 0x1.fffffep127f)) atom_or(f.status, 1);
     }
   }
-  constexpr int CG = (TW_ + 8) / 4;             // groups of 4 columns
-  constexpr int SR = TH == 64 ? 8 : 2;          // rows per item
-  constexpr int ITEMS = CG * ((TH + 8) / SR);
-  static_assert(ITEMS <= NT && (TH + 8) % SR == 0 && SR <= 8, "one item per thread");
-  uint32_t hits = 0;
-  const int sg = tid / CG, cg = tid - sg * CG;
-  const int px0 = 4 + 4 * cg, py0 = 4 + SR * sg;
+  // A lane per group of 4 columns, whole rows of the region side by side in a
+  // wave: the columns beside a group come from the lanes beside it.  (The
+  // first and last group of a row have no pixel to test.)  Reading them from
+  // LDS, a word in four of a bank, cost more than the rows themselves.
+  // Each lane's rows are pairs far apart, so that a star's pixels, listed
+  // lane by lane below, are spread over several lanes.
+  constexpr int PG = RW / 4, PRUNS = 64 / PG, PALL = NT / 64 * PRUNS;  // row pairs at once
+  constexpr int PP = (TH + 8) / (2 * PALL), PR = 2 * PP;               // a lane's pairs, rows
+  static_assert(PR * PALL == TH + 8 && 4 * PR <= 32, "the waves share the rows evenly");
+  uint32_t hits = 0;  // pixel b of row k: bit 4 PR - 1 - (4 k + b)
+  const int run = min((tid & 63) / PG, PRUNS - 1), pg = (tid & 63) - run * PG;
+  const int px0 = 4 * pg, py0 = 4 + 2 * ((tid >> 6) * PRUNS + run);
+  auto prow = [&](int k) __attribute__((always_inline)) { return py0 + (k >> 1) * (2 * PALL) + (k & 1); };
   __syncthreads();
   const float thr = s.thr;
   const bool nonneg = s.mn >= 0.0f;
-  if (tid < ITEMS) {
-    float4 up = *reinterpret_cast<const float4*>(&s.c[py0 - 1][px0]);
-    float4 cu = *reinterpret_cast<const float4*>(&s.c[py0][px0]);
+  {
 #pragma unroll
-    for (int k = 0; k < SR; ++k) {
-      const float4 dn = *reinterpret_cast<const float4*>(&s.c[py0 + k + 1][px0]);
-      const float l = s.c[py0 + k][px0 - 1], r = s.c[py0 + k][px0 + 4];
-      const float e0 = __builtin_fmaf(2.0f, cu.x, -(vmin(up.x, dn.x) + vmin(l, cu.y)));
-      const float e1 = __builtin_fmaf(2.0f, cu.y, -(vmin(up.y, dn.y) + vmin(cu.x, cu.z)));
-      const float e2 = __builtin_fmaf(2.0f, cu.z, -(vmin(up.z, dn.z) + vmin(cu.y, cu.w)));
-      const float e3 = __builtin_fmaf(2.0f, cu.w, -(vmin(up.w, dn.w) + vmin(cu.z, r)));
-      hits |= (!(e0 <= thr) ? 1u : 0u) << (4 * k);
-      hits |= (!(e1 <= thr) ? 2u : 0u) << (4 * k);
-      hits |= (!(e2 <= thr) ? 4u : 0u) << (4 * k);
-      hits |= (!(e3 <= thr) ? 8u : 0u) << (4 * k);
-      up = cu;
-      cu = dn;
+    for (int j = 0; j < PP; ++j) {
+      const int y = prow(2 * j);
+      float4 up = *reinterpret_cast<const float4*>(&s.c[y - 1][px0]);
+      float4 cu = *reinterpret_cast<const float4*>(&s.c[y][px0]);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const float4 dn = *reinterpret_cast<const float4*>(&s.c[y + k + 1][px0]);
+        const float l = dpp_move<0x138, 0xf>(cu.w), r = dpp_move<0x130, 0xf>(cu.x);  // wave_shr:1, wave_shl:1
+        const float e0 = __builtin_fmaf(2.0f, cu.x, -(vmin(up.x, dn.x) + vmin(l, cu.y)));
+        const float e1 = __builtin_fmaf(2.0f, cu.y, -(vmin(up.y, dn.y) + vmin(cu.x, cu.z)));
+        const float e2 = __builtin_fmaf(2.0f, cu.z, -(vmin(up.z, dn.z) + vmin(cu.y, cu.w)));
+        const float e3 = __builtin_fmaf(2.0f, cu.w, -(vmin(up.w, dn.w) + vmin(cu.z, r)));
+        hits = hits + hits + (!(e0 <= thr) ? 1u : 0u);
+        hits = hits + hits + (!(e1 <= thr) ? 1u : 0u);
+        hits = hits + hits + (!(e2 <= thr) ? 1u : 0u);
+        hits = hits + hits + (!(e3 <= thr) ? 1u : 0u);
+        up = cu;
+        cu = dn;
+      }
     }
+    if ((tid & 63) >= PG * PRUNS || pg == 0 || pg == PG - 1) hits = 0u;
     if (!inner && hits) {  // pixels of the frame only
 #pragma unroll
-      for (int k = 0; k < SR; ++k)
+      for (int k = 0; k < PR; ++k)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int q = px0 + b;
-          if (!row_in(py0 + k) || q < fc0 || q >= fc1) hits &= ~(1u << (4 * k + b));
+          if (!row_in(prow(k)) || q < fc0 || q >= fc1) hits &= ~(1u << (4 * PR - 1 - (4 * k + b)));
         }
     }
   }
-  const unsigned int nhit = __popc(hits);
-  const unsigned int hbase = nhit ? atomicAdd(&s.cnt, nhit) : 0u;
+  const unsigned int hbase = wave_reserve(&s.cnt, (unsigned int)__popc(hits));
   __syncthreads();
   const unsigned int npc = s.cnt;
+  uint2* open = reinterpret_cast<uint2*>(s.s4);  // candidates and their med7 bounds, before the pool's use
+  constexpr int OCAP = (int)(sizeof(s.s4) / sizeof(uint2));
   for (unsigned int c0 = 0; c0 < npc; c0 += ICAP) {  // one round unless the tile is dense
     uint32_t hb = hits;
     unsigned int at = hbase;
     while (hb) {
-      const int b = __ffs((int)hb) - 1;
+      const int b = 4 * PR - __ffs((int)hb);
       hb &= hb - 1;
-      if (at - c0 < (unsigned int)ICAP) s.lst[at - c0] = (uint16_t)((py0 + (b >> 2)) * RW + px0 + (b & 3));
+      if (at - c0 < (unsigned int)ICAP) s.lst[at - c0] = (uint16_t)(prow(b >> 2) * RW + px0 + (b & 3));
       ++at;
     }
     __syncthreads();
@@ -729,21 +800,45 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       if (S > sigclip) {
         // dead: the objlim test fails even for S' = S.  Not where it holds
         // for the smallest med7 there can be (cosmic rays); else where med7
-        // lies below the value at which it would hold (stars).
+        // lies below the value at which it would hold (stars): listed.
         const float m3 = iter_med3(s, f, r, q, nonneg);
-        bool dead = false;
-        if (!objlim_holds(f, m3, s.mn, s.nmin, S)) {
+        bool live = objlim_holds(f, m3, s.mn, s.nmin, S);
+        if (!live) {
           const float d = N * (S / f.objlim), t = m3 - d - (fabsf(m3) + d) * 0x1p-18f;
-          dead = !objlim_holds(f, m3, t, N, S) && iter_med7_le(s, f, r, q, ry0, rx0, inner, t);
+          live = objlim_holds(f, m3, t, N, S);
+          if (!live) {
+            const unsigned int at = atomicAdd(&s.nopen, 1u);
+            if (at < (unsigned int)OCAP)
+              open[at] = uint2{__float_as_uint(t), (uint32_t)i};
+            else
+              live = true;  // (evaluated in full)
+          }
         }
-        s.set(dead ? kBitDead : kBitCd, r, q);
-        if (!dead) {
+        if (live) {
+          s.set(kBitCd, r, q);
           s.live = 1;
           s.mark_near(r, q);
         }
       }
     }
     __syncthreads();
+    const unsigned int no = min(s.nopen, (unsigned int)OCAP);
+    if (no) {  // (uniform)
+      for (unsigned int j = tid >> 2; j < no; j += NT / 4) {
+        const uint2 o = open[j];
+        const int i = (int)o.y, r = i / RW, q = i - r * RW;
+        const bool dead = iter_med7_le(s, f, r, q, ry0, rx0, inner, __uint_as_float(o.x));
+        if ((tid & 3) == 0) {
+          s.set(dead ? kBitDead : kBitCd, r, q);
+          if (!dead) {
+            s.live = 1;
+            s.mark_near(r, q);
+          }
+        }
+      }
+      __syncthreads();
+      if (tid == 0) s.nopen = 0u;  // (for the next round, a barrier away)
+    }
   }
 
   // ---- 3-4. S near the live candidates of rows [b0, b1), S', G1, G2, B1.
@@ -751,9 +846,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
   // evaluate the list.  marked:
   // the blocks are marked already (by step 2, for all rows).
   auto detect = [&](int b0, int b1, bool marked) __attribute__((always_inline)) -> bool {
-    __syncthreads();  // every thread has read the counters of the round before
     next_phase();
-    if (tid == 0) s.nq = s.n2 = 0u;
     if (!marked) {
       if (tid < QR) s.qbits[tid] = 0ull;
       if (wt) s.word(kBitD1, wr, ww) = 0u;
@@ -761,72 +854,136 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       if (wt && wr >= b0 && wr < b1)
         for (uint32_t d = s.word(kBitCd, wr, ww); d; d &= d - 1) s.mark_near(wr, 32 * ww + __ffs((int)d) - 1);
     }
+    if (tid == 0) s.n2 = 0u;
     __syncthreads();
-    constexpr int QW = (QC + 31) / 32;  // words of a block row
-    if (tid < QR * QW) {
-      const int br = tid / QW, half = tid - br * QW;
-      uint64_t row = s.qbits[br];
-      if (!inner) {  // blocks that hold a pixel of the frame
-        const int j0 = max(0, (fc0 - 2) >> 1), j1 = min(QC, (fc1 - 1) >> 1);
-        const bool in = (row_in(2 + 2 * br) || row_in(3 + 2 * br)) && j0 < j1;
-        row &= in ? ((1ull << j1) - 1ull) & ~((1ull << j0) - 1ull) : 0ull;
-      }
-      uint32_t d = (uint32_t)(row >> (32 * half));
-      if (d) {
-        unsigned int at = atomicAdd(&s.nq, (unsigned int)__popc(d));
-        for (; d; d &= d - 1) {
-          const int q = br * QC + 32 * half + __ffs((int)d) - 1;
-          if (at < (unsigned int)QCAP) {
-            s.s4[at][0] = __int_as_float(q);
-            s.qmap[q] = (typename SM::QIndex)at;
-          }
-          ++at;
-        }
-      }
+    // Every wave sums up the rows' blocks, a row each lane; block j of the
+    // tile is then found from the sums, with no list.
+    static_assert(QR <= 64 && QC <= 64, "a lane per row, a bit per column");
+    const int ln = tid & 63;
+    uint64_t row = ln < QR ? s.qbits[ln] : 0ull;
+    if (!inner) {  // blocks that hold a pixel of the frame
+      const int j0 = max(0, (fc0 - 2) >> 1), j1 = min(QC, (fc1 - 1) >> 1);
+      const bool in = (row_in(2 + 2 * ln) || row_in(3 + 2 * ln)) && j0 < j1;
+      row &= in ? ((1ull << j1) - 1ull) & ~((1ull << j0) - 1ull) : 0ull;
     }
-    __syncthreads();
-    const unsigned int nq = s.nq;
-    if (nq > (unsigned int)QCAP) return false;
-    for (unsigned int j = tid; j < nq; j += NT) {
-      const int qi = __float_as_int(s.s4[j][0]), br = qi / QC;
-      const int y = 2 + 2 * br, x = 2 + 2 * (qi - br * QC);
-      float S[4];
-      iter_quad(s, f, nc, y, x, nonneg, S);
-      *reinterpret_cast<float4*>(s.s4[j]) = float4{S[0], S[1], S[2], S[3]};
+    const int upto = wave_scan(__popcll(row));
+    const unsigned int nq = (unsigned int)__builtin_amdgcn_readlane(upto, 63);
+    if (nq > (unsigned int)QCAP) {
+      __syncthreads();  // (the next round clears the marks)
+      return false;
+    }
+    // S at the pixels of block j's part: PX of its pixels, in each of 4 / PX
+    // lanes.  Those that are live candidates of the rows, or next to one with
+    // S > lo (G2 off the candidates matters within 2 pixels of the tile), are
+    // listed.  (Whole waves run this.)
+    auto blocks = [&](auto px) __attribute__((always_inline)) {
+      constexpr int PX = decltype(px)::value, LANES = 4 / PX;
+#pragma unroll 1
+      for (unsigned int j0 = 0; j0 < nq; j0 += NT / LANES) {
+        const unsigned int j = j0 + tid / LANES;
+        const int part = tid % LANES;
+        const unsigned int jc = min(j, nq - 1u);
+        int br = 0;  // the row that holds it: the first whose sum exceeds j
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int r = y + a;
-        // the live candidates of the rows, and next to one the pixels with
-        // S > lo (G2 off the candidates matters within 2 pixels of the tile)
-        const int rb = clampi(r - SM::BR0, SM::BROWS - 1) + SM::BR0;
-        const uint32_t cw = rb == r ? s.word(kBitCd, rb, x >> 5) >> (x & 31) : 0u;
-        const uint32_t dw = (s.word(kBitD1, rb, x >> 5) >> (x & 31)) & ~cw;
-        const bool rows = r >= b0 && r < b1;
-        const bool g2row = r >= 6 && r < RH - 6 && (inner || row_in(r));
+        for (int k = 32; k > 0; k >>= 1) br += __shfl(upto, br + k - 1) <= (int)jc ? k : 0;
+        const uint32_t ml = (uint32_t)__shfl((int)(uint32_t)row, br);
+        const uint32_t mh = QC > 32 ? (uint32_t)__shfl((int)(uint32_t)(row >> 32), br) : 0u;
+        const int nth = (int)jc - (__shfl(upto, br) - __popc(ml) - __popc(mh));
+        const int bc = nth_bit(ml, mh, nth);
+        const int y = 2 + 2 * br + (PX == 4 ? 0 : part * PX / 2), x = 2 + 2 * bc + (PX == 1 ? part & 1 : 0);
+        float S[PX];
+        uint32_t want = 0u;  // bit k: pixel k listed
+        if (j < nq) {
+          constexpr int ROWS = PX == 4 ? 2 : 1, COLS = PX / ROWS;
+          uint32_t cw[ROWS], dw[ROWS];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const bool g2col = x + b >= 6 && x + b < RW - 6 && (inner || (x + b >= fc0 && x + b < fc1));
-          if ((((cw >> b) & 1u) && rows) || (((dw >> b) & 1u) && g2row && g2col && S[2 * a + b] > lo))
-          {
-            const unsigned int at = atomicAdd(&s.n2, 1u);
-            if (at < (unsigned int)ICAP) s.lst[at] = (uint16_t)(r * RW + x + b);
+          for (int a = 0; a < ROWS; ++a) {
+            const int rb = clampi(y + a - SM::BR0, SM::BROWS - 1) + SM::BR0;
+            cw[a] = s.word(kBitCd, rb, x >> 5) >> (x & 31);
+            dw[a] = s.word(kBitD1, rb, x >> 5) >> (x & 31);
+            if (rb != y + a) cw[a] = 0u;
+          }
+          iter_block<PX>(s, f, nc, y, x, nonneg, S);
+          if (PX == 4)
+            *reinterpret_cast<float4*>(s.s4[j]) = float4{S[0], S[1 % PX], S[2 % PX], S[3 % PX]};
+          else if (PX == 2)
+            *reinterpret_cast<float2*>(&s.s4[j][2 * part]) = float2{S[0], S[1 % PX]};
+          else
+            s.s4[j][part] = S[0];
+          if (part == 0) s.qmap[br * QC + bc] = (typename SM::QIndex)j;
+#pragma unroll
+          for (int k = 0; k < PX; ++k) {
+            const int a = k / COLS, b = k % COLS, r = y + a, q = x + b;
+            const bool cand = (cw[a] >> b) & 1u, by = (dw[a] >> b) & 1u;
+            const bool here = r >= 6 && r < RH - 6 && q >= 6 && q < RW - 6 &&
+                              (inner || (row_in(r) && q >= fc0 && q < fc1));
+            if (cand ? r >= b0 && r < b1 : by && here && S[k] > lo) want |= 1u << k;
           }
         }
+        unsigned int at = wave_reserve(&s.n2, (unsigned int)__popc(want));
+#pragma unroll
+        for (int k = 0; k < PX; ++k)
+          if ((want >> k) & 1u) {
+            if (at < (unsigned int)ICAP) s.lst[at] = (uint16_t)((y + k / 2 * (PX == 4 ? 1 : 0)) * RW + x + (PX == 1 ? 0 : k & 1));
+            ++at;
+          }
       }
-    }
+    };
+    // A block's four medians together take 308 operations, two of a row 212,
+    // one alone 206: fewer blocks than lanes, less work per lane.
+    if (4 * nq <= (unsigned int)NT)
+      blocks(std::integral_constant<int, 1>{});
+    else if (2 * nq <= (unsigned int)NT)
+      blocks(std::integral_constant<int, 2>{});
+    else
+      blocks(std::integral_constant<int, 4>{});
     __syncthreads();
     next_phase();
     const unsigned int n2 = s.n2;
-    if (n2 > (unsigned int)ICAP) return false;
-    for (unsigned int j = tid; j < n2; j += NT) {
-      const int i = s.lst[j], r = i / RW, q = i - r * RW;
-      const float spv = iter_sprime(s, f, r, q, ry0, rx0, inner);
-      if (spv > lo) s.set(kBitG2, r, q);
-      if (spv > sigclip) {
-        s.set(kBitG1, r, q);
-        if (iter_objlim(s, f, nc, r, q, ry0, rx0, inner, nonneg, spv)) {
-          s.set(kBitB1, r, q);
-          s.any_b1 = 1;
+    if (n2 > (unsigned int)ICAP) {
+      __syncthreads();
+      return false;
+    }
+#pragma unroll 1
+    for (unsigned int j0 = 0; j0 < n2; j0 += NT) {
+      const unsigned int j = j0 + tid;
+      int i = 0;
+      float limit = 0.0f;
+      bool open = false;
+      if (j < n2) {
+        i = s.lst[j];
+        const int r = i / RW, q = i - r * RW;
+        const float spv = iter_sprime(s, f, r, q, ry0, rx0, inner);
+        if (spv > lo) s.set(kBitG2, r, q);
+        if (spv > sigclip) {
+          s.set(kBitG1, r, q);
+          // holds for the smallest med7 and N there can be?
+          const float m3 = iter_med3(s, f, r, q, nonneg);
+          open = !objlim_holds(f, m3, s.mn, s.nmin, spv);
+          if (open) {
+            limit = iter_objlim(s, f, nc, r, q, nonneg, m3, spv);
+          } else {
+            s.set(kBitB1, r, q);
+            s.any_b1 = 1;
+          }
+        }
+      }
+      const uint64_t left = __ballot(open);
+      if (left) {  // (uniform) the wave's undecided ones, a quad each
+        const int ln = tid & 63, total = __popcll(left);
+        const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(left >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)left, 0u));
+        // lane k gets the k-th one's lane
+        const int nth = __builtin_amdgcn_ds_permute(4 * (open ? before : total + ln - before), ln);
+#pragma unroll 1
+        for (int k0 = 0; k0 < total; k0 += 16) {
+          const int k = k0 + (ln >> 2), src = __shfl(nth, min(k, 63));
+          const int ci = __shfl(i, src), r = ci / RW, q = ci - r * RW;
+          const float lim = __shfl(limit, src);
+          if (k < total && !iter_med7_le(s, f, r, q, ry0, rx0, inner, lim) && (ln & 3) == 0) {
+            s.set(kBitB1, r, q);
+            s.any_b1 = 1;
+          }
         }
       }
     }
@@ -841,8 +998,8 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     // ray beside a star): dead candidates within 1 of a live one are
     // evaluated with the live ones
     {
+      // (one that a promoted one brings in as well costs work, no more)
       const uint32_t up = wt ? s.word(kBitDead, wr, ww) & s.word(kBitD1, wr, ww) : 0u;
-      __syncthreads();
       if (up) {
         atomicOr(&s.word(kBitCd, wr, ww), up);
         for (uint32_t d = up; d; d &= d - 1) s.mark_near(wr, 32 * ww + __ffs((int)d) - 1);
@@ -865,6 +1022,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
   next_phase();
   if (s.any_b1) {  // (uniform: written before a barrier, read after it)
     if (tid == 0) s.cnt = 0u;
+    uint32_t fresh = 0u;
     if (wt) {
       uint32_t nw = 0u;
       if (wr >= 6 && wr < RH - 6) {
@@ -886,10 +1044,11 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
         nw = b3 & ~m;
         s.word(kBitM, wr, ww) = m | b3;
         const uint32_t own = nw & col_bits(ww, HL, HL + TW_);
-        if (wr >= HL && wr < HL + TH && own) atomicAdd(&s.fresh, (unsigned int)__popc(own));
+        if (wr >= HL && wr < HL + TH) fresh = (uint32_t)__popc(own);
       }
       s.word(kBitCd, wr, ww) = nw;  // the new mask pixels
     }
+    (void)wave_reserve(&s.fresh, fresh);
     __syncthreads();
     if (!inner) {  // the replacement's windows clamp on the frame too
       uint32_t m = 0u;
@@ -905,7 +1064,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     }
     // the tile's mask pixels: those within 2 of a new one are replaced anew,
     // the others keep their value
-    uint32_t redo = 0u, keep = 0u;
+    uint32_t redo = 0u, keep = 0u, zone = 0u;
     if (wt && wr >= HL && wr < HL + TH && row_in(wr)) {
       const uint32_t own = s.word(kBitM, wr, ww) & col_bits(ww, HL, min(HL + TW_, fc1));
       if (own) {
@@ -920,12 +1079,13 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
           const uint32_t z = ((redo & col_bits(ww, HL, 2 * HL)) ? 1u : 0u) |
                              ((redo & col_bits(ww, 2 * HL, TW_)) ? 2u : 0u) |
                              ((redo & col_bits(ww, TW_, TW_ + HL)) ? 4u : 0u);
-          atomicOr(&s.zones, z << (3 * zy));
+          zone = z << (3 * zy);
         }
       }
     }
-    const unsigned int nr = __popc(redo);
-    const unsigned int rbase = nr ? atomicAdd(&s.cnt, nr) : 0u;
+    zone = wave_or(zone);
+    if (zone && lane == 0) atomicOr(&s.zones, zone);
+    const unsigned int rbase = wave_reserve(&s.cnt, (unsigned int)__popc(redo));
     __syncthreads();
     const unsigned int nredo = s.cnt;
     changed = nredo != 0u;  // (uniform)
@@ -997,18 +1157,15 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
           if (it > 0) {
             stg(f.clean, gi, out);
             stg(f.out_mask, gi, (uint8_t)1);
+          } else {
+            s.c[r][q] = out;  // the whole tile is stored below, from LDS; a mask pixel, so no window holds it
           }
         }
-        if (it == 0) {  // the whole tile is stored below, from LDS
-          __syncthreads();
-          if (j < n) s.c[r][q] = out;
-          __syncthreads();
-        }
       }
+      if (unrep) atomicAdd(&s.unrep, unrep);
+      unrep = 0u;
       __syncthreads();  // the list is rebuilt
     }
-    if (unrep) atomicAdd(&s.unrep, unrep);
-    __syncthreads();
     if (tid == 0) {
       if (s.fresh) atom_add(f.n_new + it, (unsigned long long)s.fresh);
       if (s.unrep) atom_add(f.n_new + f.niter, (unsigned long long)s.unrep);

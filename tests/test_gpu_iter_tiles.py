@@ -104,3 +104,23 @@ def test_values_where_the_bounds_overflow():
     _check(img, gain=2.0 ** -40, niter=2, flags=False)  # the read noise covers everything
     _check((img * F32(2.0 ** 40)).astype(F32), gain=2.0 ** -40, niter=2)
     _check((img * F32(1e-30)).astype(F32), gain=1.0, rn=0.0, niter=2, flags=False)  # all below the floor
+
+
+@pytest.mark.parametrize("sepmed", [False, True])
+@pytest.mark.parametrize("shape,most", [((512, 544), 60), ((1088, 1024), 110)])
+def test_tiles_of_every_load(shape, most, sepmed):
+    # from tile to tile, 0 .. most isolated bright pixels, and star cores of as
+    # many rejected pixels: all block counts from none to past the pool, a few
+    # and many candidates whose objlim test is close
+    h, w = shape
+    g = np.random.Generator(np.random.PCG64(99))
+    img = g.poisson(200.0, size=shape) + g.normal(0, 5.0, size=shape)
+    e = 32 if h * w <= 1 << 20 else 64
+    for k, (y, x) in enumerate((y, x) for y in range(0, h, e) for x in range(0, w, e)):
+        n = k * 7 % (most + 1)
+        img[y + g.integers(0, min(e, h - y), n), x + g.integers(0, min(e, w - x), n)] += g.uniform(150, 900, n)
+        if k % 3 == 0:
+            yy, xx = np.mgrid[y:min(y + e, h), x:min(x + e, w)]
+            s = 1.2 + 0.25 * (k % 17)
+            img[yy, xx] += 40000.0 * np.exp(-((yy - y - e / 2) ** 2 + (xx - x - e / 2) ** 2) / (2 * s * s))
+    _check(img.astype(F32), niter=4, sepmed=sepmed)

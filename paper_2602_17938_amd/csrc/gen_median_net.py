@@ -163,28 +163,6 @@ def merge_trimmed(net, a, b, lo, hi):
     return m
 
 
-def median_of_sorted_lists(net, lists, n_total=None, med=None):
-    """Median (rank med of n_total) of the union of sorted wire lists."""
-    n = n_total if n_total is not None else sum(len(x) for x in lists)
-    med = (n - 1) // 2 if med is None else med
-    # each part: [wires, dropped_low, coverage]
-    parts = [[list(x), 0, len(x)] for x in lists]
-    while len(parts) > 1:
-        parts.sort(key=lambda p: p[2])
-        (wa, da, ca), (wb, db, cb) = parts[0], parts[1]
-        cov = ca + cb
-        drop = da + db
-        t = n - cov
-        lo_rank = max(0, med - t)
-        hi_rank = min(med, cov - 1)
-        if t == 0 and len(parts) == 2:
-            return net.select_rank(wa, wb, med - drop)
-        w = merge_trimmed(net, wa, wb, lo_rank - drop, hi_rank - drop)
-        parts = parts[2:] + [[w, lo_rank, cov]]
-    wires, drop, cov = parts[0]
-    return wires[med - drop]
-
-
 def line_median_net(k):
     """Median of k keys in a line (a row or a column of a window).  Five
     keys: the larger of the two pairs' minima and the smaller of their maxima
@@ -205,10 +183,16 @@ def line_median_net(k):
 
 
 def window_median_net(k):
-    """Median of a k x k window, inputs v[r*k + c]."""
-    net = Net(k * k)
-    cols = [net.sort([r * k + c for r in range(k)]) for c in range(k)]
-    out = median_of_sorted_lists(net, cols)
+    """Median of a k x k window, inputs v[r*k + c]: the columns of all rows
+    but the first, sorted and merged pairwise, each merge trimmed to the
+    ranks that can still hold the median; then the first row's cells, the
+    same way.  184 operations for k = 5 and 542 for 7, where merging whole
+    sorted columns took 206 and 570."""
+    n, med = k * k, (k * k - 1) // 2
+    net = Net(n)
+    cols = [[net.sort([r * k + c for r in range(1, k)]), 0, k - 1] for c in range(k)]
+    parts = _trim_merge_all(net, cols, n, med, False)
+    out = _trim_merge_all(net, parts + [[[c], 0, 1] for c in range(k)], n, med, True)
     net.prune([out])
     return net, out
 

@@ -529,9 +529,10 @@ struct IterGrid {
 };
 
 // The iteration on one tile, by kIterThreads threads; every barrier is
-// block-uniform.
+// block-uniform.  news: 0 if the iteration does not run (looked at only when
+// the first loads are on their way).
 template <int TH, int TW_>
-__device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, const IterList& next,
+__device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, const IterList& next, unsigned long long news,
                                           SmemIter<TH, TW_>& s) {
   using SM = SmemIter<TH, TW_>;
   constexpr int NT = kIterThreads, RH = SM::RH, RW = SM::RW, QR = SM::QR, QC = SM::QC, NW = SM::NW;
@@ -545,15 +546,14 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
   const int ty = tile / grid.tiles_x, tx = tile - ty * grid.tiles_x;
   const int y0 = ty * TH, x0 = tx * TW_;
   const int ry0 = y0 - HL, rx0 = x0 - HL;
-  uint32_t st[9];  // planes of the 3x3 tiles after the previous iteration
+  // Everything the tile starts from is read at once (each load is a round trip
+  // to memory, and one that waits for another's answer makes two): the state
+  // words, both planes' mask words, and the input.
+  uint32_t state = 0u;
   if (it > 0) {
     const int n = grid.neighbour(ty, tx, lane < 9 ? lane : 4);
-    const uint32_t v = __hip_atomic_load(gp(iter_state(f) + max(n, 0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t p = (v & 1u) ^ ((v >> 1) == (uint32_t)(it + 1) ? 1u : 0u);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) st[k] = (uint32_t)__builtin_amdgcn_readlane((int)p, k);
+    state = __hip_atomic_load(gp(iter_state(f) + max(n, 0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  const uint32_t plane = it > 0 ? st[4] : 1u;  // this iteration writes plane ^ 1
   const bool inner = ry0 >= 0 && rx0 >= 0 && ry0 + RH <= h && rx0 + RW <= w;
   const int fc0 = rx0 < 0 ? -rx0 : 0, fc1 = min(RW, w - rx0);  // region columns inside the frame
   auto row_in = [&](int r) __attribute__((always_inline)) { return ry0 + r >= 0 && ry0 + r < h; };
@@ -567,6 +567,72 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
   };
 
   // ---- 1. stage C_k and M_k
+  const int mr = tid / NW, mq = tid - mr * NW;  // this thread's word of M_k
+  static_assert(RH * NW <= NT, "one thread per word of M_k");
+  typedef typename std::conditional<TW_ == 64, uint64_t, uint32_t>::type MWord;
+  const bool mrow = it > 0 && mr < RH && row_in(mr);
+  MWord mown[2] = {0, 0}, mside[2] = {0, 0};  // by plane: the tile's own columns, and 8 of a neighbour
+  if (mrow) {
+    const int side = mq == 0 ? tx - 1 : tx + 1;
+    const bool beside = (mq == 0 || mq == NW - 1) && side >= 0 && side < grid.tiles_x;
+    const int64_t at = (int64_t)(ry0 + mr) * f.wpr * (TW_ == 64 ? 1 : 2);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const MWord* m = reinterpret_cast<const MWord*>(f.mbits[p]);
+      mown[p] = ldg(m, at + tx);
+      if (beside) mside[p] = ldg(m, at + side);
+    }
+  }
+  // C4 threads per row of 4 pixels each, RP rows at a time
+  constexpr int C4 = RW / 4, RP = NT / C4, K = (RH + RP - 1) / RP;
+  typedef uint16_t h4u __attribute__((ext_vector_type(4), aligned(2)));
+  const int r0 = tid / C4, q0 = 4 * (tid - r0 * C4);
+  const float* src = f.img;
+  const uint16_t* src16 = f.img16;
+  uint4 raw[K];
+  if (inner) {
+    const uint32_t o0 = (uint32_t)(r0 * w + q0), step = (uint32_t)(RP * w);  // from the region's corner
+    const int64_t corner = (int64_t)ry0 * w + rx0;
+    // (threads and rows past the region load its first rows again)
+    auto at = [&](int k) __attribute__((always_inline)) -> uint32_t {
+      return (r0 + k * RP < RH) ? o0 + (uint32_t)k * step : o0;
+    };
+    if (src16) {
+      const uint16_t* base = src16 + corner;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const h4u v = *(const __attribute__((address_space(1))) h4u*)(base + at(k));
+        const uint2 u = __builtin_bit_cast(uint2, v);
+        raw[k].x = u.x;
+        raw[k].y = u.y;
+      }
+    } else {
+      const float* base = src + corner;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        raw[k] = __builtin_bit_cast(uint4, (f4u) * (const __attribute__((address_space(1))) f4u*)(base + at(k)));
+    }
+  } else {  // clamped on the frame, pixel by pixel
+    int cx[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) cx[b] = clampi(rx0 + q0 + b, w - 1);
+    auto row = [&](int k) __attribute__((always_inline)) {
+      return (int64_t)clampi(ry0 + min(r0 + k * RP, RH - 1), h - 1) * w;
+    };
+    if (src16) {  // (chosen per load instead, each load would wait for the one before)
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint16_t* p = src16 + row(k);
+        raw[k] = uint4{ldg(p, cx[0]), ldg(p, cx[1]), ldg(p, cx[2]), ldg(p, cx[3])};
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint32_t* p = reinterpret_cast<const uint32_t*>(src + row(k));
+        raw[k] = uint4{ldg(p, cx[0]), ldg(p, cx[1]), ldg(p, cx[2]), ldg(p, cx[3])};
+      }
+    }
+  }
   if (tid == 0) {
     s.cnt = 0u;
     s.nopen = 0u;
@@ -576,82 +642,48 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     s.any_b1 = 0;
     s.live = 0;
   }
-  const float* src = f.img;
-  const uint16_t* src16 = f.img16;
-  float mn = __int_as_float(0x7f800000), mx = 0.0f;
+  uint32_t st[9];  // planes of the 3x3 tiles after the previous iteration
+  if (it > 0) {
+    const uint32_t p = (state & 1u) ^ ((state >> 1) == (uint32_t)(it + 1) ? 1u : 0u);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) st[k] = (uint32_t)__builtin_amdgcn_readlane((int)p, k);
+  }
+  const uint32_t plane = it > 0 ? st[4] : 1u;  // this iteration writes plane ^ 1
+  if (news == 0ull) return;
   uint32_t mword = 0u;  // M_k: word mq of region row mr
-  const int mr = tid / NW, mq = tid - mr * NW;
-  static_assert(RH * NW <= NT, "one thread per word of M_k");
-  if (it > 0 && mr < RH && row_in(mr)) {
-    // the tile's own columns and 8 of each neighbour
-    const int64_t gy = ry0 + mr;
+  if (mrow) {
     const uint32_t sl = mr < HL ? st[0] : mr < HL + TH ? st[3] : st[6];
     const uint32_t sc = mr < HL ? st[1] : mr < HL + TH ? st[4] : st[7];
     const uint32_t sr = mr < HL ? st[2] : mr < HL + TH ? st[5] : st[8];
-    auto word = [&](uint32_t p, int t) __attribute__((always_inline)) -> uint64_t {
-      if (t < 0 || t >= grid.tiles_x) return 0ull;
-      const uint64_t* m = p ? f.mbits[1] : f.mbits[0];
-      if (TW_ == 64) return ldg(m, gy * f.wpr + t);
-      return ldg(reinterpret_cast<const uint32_t*>(m), gy * f.wpr * 2 + t);
-    };
-    const uint64_t cw = word(sc, tx);
-    if (mq == 0) mword = (uint32_t)((word(sl, tx - 1) >> (TW_ - 8)) & 0xffull) | ((uint32_t)cw << 8);
-    if (mq == NW - 1) mword = (uint32_t)(cw >> (TW_ - 8)) | ((uint32_t)(word(sr, tx + 1) & 0xffull) << 8);
+    const uint64_t cw = sc ? mown[1] : mown[0];
+    const uint64_t dw = (mq == 0 ? sl : sr) ? mside[1] : mside[0];
+    if (mq == 0) mword = (uint32_t)((dw >> (TW_ - 8)) & 0xffull) | ((uint32_t)cw << 8);
+    if (mq == NW - 1) mword = (uint32_t)(cw >> (TW_ - 8)) | ((uint32_t)(dw & 0xffull) << 8);
     if (NW == 3 && mq == 1) mword = (uint32_t)(cw >> 24);
   }
-  {
-    // C4 threads per row of 4 pixels each, RP rows at a time
-    constexpr int C4 = RW / 4, RP = NT / C4, K = (RH + RP - 1) / RP;
-    typedef uint16_t h4u __attribute__((ext_vector_type(4), aligned(2)));
-    const int r0 = tid / C4, q0 = 4 * (tid - r0 * C4);
-    auto put = [&](int k, float a, float b, float c, float d) __attribute__((always_inline)) {
-      const int r = r0 + k * RP;
-      if (RP * C4 != NT && r0 >= RP) return;
-      if (K * RP != RH && r >= RH) return;
-      a += 0.0f;  // -0 becomes +0
-      b += 0.0f;
-      c += 0.0f;
-      d += 0.0f;
-      mn = vmin3(vmin3(mn, a, b), c, d);
-      mx = vmax3_abs(vmax3_abs(mx, a, b), c, d);
-      *reinterpret_cast<float4*>(&s.c[r][q0]) = float4{a, b, c, d};
-    };
-    if (inner) {
-      const uint32_t o0 = (uint32_t)(r0 * w + q0), step = (uint32_t)(RP * w);  // from the region's corner
-      const int64_t corner = (int64_t)ry0 * w + rx0;
-      // (threads and rows past the region load its first rows again)
-      auto at = [&](int k) __attribute__((always_inline)) -> uint32_t {
-        return (r0 + k * RP < RH) ? o0 + (uint32_t)k * step : o0;
-      };
-      if (src16) {
-        const uint16_t* base = src16 + corner;
-        h4u v[K];
+  float mn = __int_as_float(0x7f800000), mx = 0.0f;
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) h4u*)(base + at(k));
-#pragma unroll
-        for (int k = 0; k < K; ++k) put(k, (float)v[k].x, (float)v[k].y, (float)v[k].z, (float)v[k].w);
-      } else {
-        const float* base = src + corner;
-        f4u v[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = *(const __attribute__((address_space(1))) f4u*)(base + at(k));
-#pragma unroll
-        for (int k = 0; k < K; ++k) put(k, v[k].x, v[k].y, v[k].z, v[k].w);
-      }
-    } else {  // clamped on the frame, pixel by pixel
-      int cx[4];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) cx[b] = clampi(rx0 + q0 + b, w - 1);
-      float v[K][4];
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const int64_t row = (int64_t)clampi(ry0 + min(r0 + k * RP, RH - 1), h - 1) * w;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) v[k][b] = src16 ? (float)ldg(src16, row + cx[b]) : ldg(src, row + cx[b]);
-      }
-#pragma unroll
-      for (int k = 0; k < K; ++k) put(k, v[k][0], v[k][1], v[k][2], v[k][3]);
+  for (int k = 0; k < K; ++k) {
+    const int r = r0 + k * RP;
+    float a, b, c, d;
+    if (!src16) {
+      a = __uint_as_float(raw[k].x), b = __uint_as_float(raw[k].y);
+      c = __uint_as_float(raw[k].z), d = __uint_as_float(raw[k].w);
+    } else if (inner) {
+      a = (float)(raw[k].x & 0xffffu), b = (float)(raw[k].x >> 16);
+      c = (float)(raw[k].y & 0xffffu), d = (float)(raw[k].y >> 16);
+    } else {
+      a = (float)raw[k].x, b = (float)raw[k].y, c = (float)raw[k].z, d = (float)raw[k].w;
     }
+    if (RP * C4 != NT && r0 >= RP) continue;
+    if (K * RP != RH && r >= RH) continue;
+    a += 0.0f;  // -0 becomes +0
+    b += 0.0f;
+    c += 0.0f;
+    d += 0.0f;
+    mn = vmin3(vmin3(mn, a, b), c, d);
+    mx = vmax3_abs(vmax3_abs(mx, a, b), c, d);
+    *reinterpret_cast<float4*>(&s.c[r][q0]) = float4{a, b, c, d};
   }
   if (!inner)  // edge tiles read blocks no one lists (and drop what they hold)
     for (int i = tid; i < QR * QC; i += NT) s.qmap[i] = 0;
@@ -930,7 +962,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       }
     };
     // A block's four medians together take 308 operations, two of a row 212,
-    // one alone 206: fewer blocks than lanes, less work per lane.
+    // one alone 184: fewer blocks than lanes, less work per lane.
     if (4 * nq <= (unsigned int)NT)
       blocks(std::integral_constant<int, 1>{});
     else if (2 * nq <= (unsigned int)NT)

@@ -112,20 +112,30 @@ __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter(const FrameDe
                                                                    bool listed) {
   __shared__ SmemIter<TH, TW_> s;
   const FrameDev f = *fp;
-  if (stopped(f, it)) return;  // the outputs already hold the result
+  // (The list is empty if the iteration before found nothing new.  With the
+  // gain estimated the check comes before the loads: a stopped frame runs all
+  // its tiles in every launch.)
+  // (Read here, before anything else, it is a scalar load: the next counter, in
+  // the same line, is being added to, and vector loads of the line waited on
+  // those atomics, 165 against 100 us for iteration 1 of a 4000 x 6500 frame.)
+  const unsigned long long news = !listed && it > 0 && f.early_stop ? ldg(f.n_new, it - 1) : 1ull;
+  if (f.est_gain && news == 0ull) return;
   // the lists alternate between two planes no one-launch iteration uses
   const IterList next{reinterpret_cast<int*>((it & 1) ? f.splane : f.sp), f.counts + it + 1, 0};
-  if (!listed) {
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
-    if (iter_due(f, it, t)) tile_iter<TH, TW_>(f, it, t, next, s);
+  if (!listed) {  // (every tile is due)
+    tile_iter<TH, TW_>(f, it, xcd_remap(blockIdx.x, gridDim.x), next, news, s);
     return;
   }
   const int* list = reinterpret_cast<const int*>((it & 1) ? f.sp : f.splane);
+  int t = ldg(list, blockIdx.x);  // (a list has room for every tile; read with its length, not after it)
   const unsigned int n = ldg(f.counts, it);
 #pragma unroll 1
   for (unsigned int i = blockIdx.x; i < n; i += gridDim.x) {
-    tile_iter<TH, TW_>(f, it, __builtin_amdgcn_readfirstlane(ldg(list, i)), next, s);
-    __syncthreads();  // the next tile reuses the LDS
+    if (i != blockIdx.x) {
+      __syncthreads();  // the LDS is used again
+      t = ldg(list, i);
+    }
+    tile_iter<TH, TW_>(f, it, __builtin_amdgcn_readfirstlane(t), next, 1ull, s);
   }
 }
 
@@ -166,7 +176,7 @@ __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(
     const FrameDev f = frames[fi];
     const int fit = it >= 0 ? it : f.it;
     const IterList next{it >= 0 ? lists + (int64_t)((it + 1) & 1) * total : nullptr, counts + it + 1, b0};
-    if (!stopped(f, fit) && (listed || iter_due(f, fit, t - b0))) tile_iter<TH, TW_>(f, fit, t - b0, next, s);
+    if (!stopped(f, fit) && (listed || iter_due(f, fit, t - b0))) tile_iter<TH, TW_>(f, fit, t - b0, next, 1ull, s);
     if (listed) __syncthreads();  // the next tile reuses the LDS
   }
 }

@@ -579,15 +579,15 @@ __device__ __forceinline__ void gain_pass(const FrameDev& f, int it, int bx, int
     }
   if (P == 0 && threadIdx.x < 4 && sh.wide[threadIdx.x]) atom_add(&g->wide[threadIdx.x], sh.wide[threadIdx.x]);
   if (P == 0 && threadIdx.x == 0 && sh.below) atom_add(&g->below, sh.below);
-  // the last block of the frame to finish takes the round's decisions
+  // The last block of the frame to finish takes the round's decisions.  Blocks
+  // share nothing but device-scope atomics, so a block has published its part
+  // when they are answered; a device-scope fence would write the XCD's L2 back
+  // as well, once for each block.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    sh.last = atom_add(&g->blocks_done, 1u) == (unsigned int)(nbx - 1) ? 1 : 0;
-  }
+  if (threadIdx.x == 0) sh.last = atom_add(&g->blocks_done, 1u) == (unsigned int)(nbx - 1) ? 1 : 0;
   __syncthreads();
   if (!sh.last) return;
-  __threadfence();
   if (P == 0) {
     unsigned int c = 0;
 #pragma unroll

@@ -42,17 +42,20 @@
 // Every value that decides anything is computed by the expressions of the
 // sparse path, so the results are the same bit for bit.
 //
-// What bounds it: vector issue and the latency of its phases together (about
-// half the issue slots of a 4096^2 frame's iteration 0, 7.3 k VALU
-// instructions per 64 x 64 tile; a block's dozen phases are separated by
-// barriers, and the sparse ones keep one to three of its four waves busy), so
-// the LDS is cut to 40 KB and the registers to 128 for four blocks per CU
-// (three blocks: 179 -> 140 us for that iteration), and each phase lists its
-// work and runs it on full waves.  Against the chain of about seven launches
-// per iteration of the sparse passes (single frames, four iterations): 512^2
-// 0.179 -> 0.132 ms with the call, 800^2 with eight times the cosmic rays
-// 0.417 -> 0.172, 4096^2 0.479 -> 0.365, 4000 x 6500 0.635 -> 0.468,
-// 6400 x 9600 0.731 -> 0.659.
+// What bounds it: the latency of a block's phases.  A block's dozen phases are
+// separated by barriers, and the sparse ones (64 bound hits, 110 blocks of S,
+// 17 tests, 12 replacements in a 64 x 64 tile of a star field) keep one to
+// three of its four waves busy: alone on a CU such a tile takes 44 k cycles in
+// iteration 0, with three others beside it 49 k, and the issue slots are half
+// used.  So the LDS is cut to 40 KB and the registers to 128 for four blocks
+// per CU (three blocks: 179 -> 140 us for iteration 0 of a 4096^2 frame when
+// that was done), the first loads of a tile are issued together, list places
+// are reserved by a scan and one atomic per wave, and work too small for the
+// block is split over more lanes.  Against the chain of about seven launches
+// per iteration of the sparse passes (single frames, four iterations, the
+// whole call): 512^2 0.173 -> 0.088 ms, 800^2 with eight times the cosmic rays
+// 0.416 -> 0.107, 2049 x 3001 separable 0.406 -> 0.181, 4096^2 0.487 -> 0.263,
+// 4000 x 6500 0.637 -> 0.347, 6400 x 9600 uint16 0.727 -> 0.512.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

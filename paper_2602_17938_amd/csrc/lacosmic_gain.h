@@ -39,7 +39,7 @@
 // 31-20, 19-10, 9-0), each a histogram of the values in the interval that
 // share the digits found so far.  The first pass of a round also forms the
 // sums.  Each pass is one launch over the frame's pixels; its last block to
-// finish (a counter taken after a device-scope fence) reads the histogram
+// finish (a counter raised when its sums are published) reads the histogram
 // and sums, takes the round's decisions and clears them for the next pass.
 // From the second round on the median moves by little (the clipped values are
 // few), so the first pass also counts the values at each of the 16384 keys

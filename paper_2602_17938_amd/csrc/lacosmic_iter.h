@@ -85,7 +85,7 @@ __device__ __forceinline__ uint32_t* iter_stamp(const FrameDev& f, int it) {
 }
 // The next iteration's list of tiles.
 struct IterList {
-  int* list;            // null: stamps only
+  int* list;
   unsigned int* count;  // its length so far
   int base;             // added to the frame's tile index
 };
@@ -1228,7 +1228,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     if (n >= 0 && (s.zones & zr & zc)) {
       const uint32_t stamp = (uint32_t)(it + 2);
       if (__hip_atomic_exchange(gp(iter_stamp(f, it + 1) + n), stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) !=
-              stamp && next.list)
+          stamp)
         stg(next.list, atom_add(next.count, 1u), next.base + n);
     }
   }

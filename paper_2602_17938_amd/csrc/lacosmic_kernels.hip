@@ -157,9 +157,9 @@ __device__ __forceinline__ int frame_of_wave(const int* base, int nframes, int t
 }
 
 // The same over the tiles of many frames (tile_base: prefix sums of their
-// TH x TW_ tile counts).  it < 0: each frame runs its own FrameDev::it (and
-// no list is kept).  lists: two lists of as many entries as there are tiles,
-// used in turn; counts: their lengths by iteration (cleared before the run).
+// TH x TW_ tile counts).  lists: two lists of as many entries as there are
+// tiles, used in turn; counts: their lengths by iteration (cleared before the
+// run).
 template <int TH, int TW_>
 __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(
     const FrameDev* __restrict__ frames, const int* tile_base, int nframes, int it, bool listed, int* lists,
@@ -174,9 +174,9 @@ __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter_frames(
     const int fi = frame_of_wave(tile_base, nframes, t);
     const int b0 = __builtin_amdgcn_readfirstlane(ldg(tile_base, fi));
     const FrameDev f = frames[fi];
-    const int fit = it >= 0 ? it : f.it;
-    const IterList next{it >= 0 ? lists + (int64_t)((it + 1) & 1) * total : nullptr, counts + it + 1, b0};
-    if (!stopped(f, fit) && (listed || iter_due(f, fit, t - b0))) tile_iter<TH, TW_>(f, fit, t - b0, next, 1ull, s);
+    const IterList next{lists + (int64_t)((it + 1) & 1) * total, counts + it + 1, b0};
+    // (beside frames that estimate their gain, others run without a list too)
+    if (!stopped(f, it) && (listed || iter_due(f, it, t - b0))) tile_iter<TH, TW_>(f, it, t - b0, next, 1ull, s);
     if (listed) __syncthreads();  // the next tile reuses the LDS
   }
 }
@@ -708,7 +708,7 @@ int64_t iter_tiles(int64_t h, int64_t w, int shape) {
 
 hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, bool all, hipStream_t st) {
   if (a.blocks <= 0) return hipSuccess;
-  const bool listed = it >= 0 && iter_listed(it, all);
+  const bool listed = iter_listed(it, all);
   const unsigned nb = (unsigned)iter_blocks(a.blocks, listed);
   if (shape == kIterSmall)
     k_iter_frames<32, 32><<<nb, kIterThreads, 0, st>>>(a.frames, a.tile_base, a.nframes, it, listed, a.lists,

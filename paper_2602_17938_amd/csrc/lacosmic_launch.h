@@ -126,9 +126,8 @@ hipError_t launch_queue_pass(const QueueArgs& a, int pass, int it, int cfg, int 
                              hipStream_t st);
 // One iteration of every frame of a table in one launch (lacosmic_iter.h):
 // a.tile_base and a.blocks count the shape's tiles, a.lists has room for two
-// lists of them and a.cursors, cleared before the run, niter + 1 lengths (both
-// unused with it < 0); it as above.  all: every tile has work (some frame
-// estimates its gain).
+// lists of them and a.cursors, cleared before the run, niter + 1 lengths.
+// all: a block per tile in every iteration (some frame estimates its gain).
 hipError_t launch_iter_frames(const QueueArgs& a, int it, int shape, bool all, hipStream_t st);
 // Gain estimate of iteration it (it < 0: each frame's own FrameDev::it) for
 // the frames of a table (one frame: its record) that estimate their gain:

@@ -23,6 +23,8 @@
 //      a margin for the rounding, has S <= sigclip.  It costs 5 operations
 //      per pixel where S costs 126.  The rest (about 1 % of the pixels of
 //      the workloads, twice the number of true candidates) get S exactly.
+//      Where they are too many, v being a defect's, a bound on the noise of
+//      each pixel's own window takes its place.
 //   3. S at the pixels within 3 of a candidate, by aligned 2x2 blocks
 //      sharing one median network, kept in an LDS pool (S' at the pixels
 //      within 1 of a candidate reads no other).
@@ -110,6 +112,14 @@ __device__ __forceinline__ uint32_t span_dil(BitSpan s) {
   for (int k = 1; k <= R; ++k)
     o |= __builtin_amdgcn_alignbit(s.c, s.l, 32 - k) | __builtin_amdgcn_alignbit(s.r, s.c, k);
   return o;
+}
+// n shifted up by one, the sign of x below.
+__device__ __forceinline__ uint32_t sign_into(uint32_t n, float x) {
+  return __builtin_amdgcn_alignbit(n, __float_as_uint(x), 31);
+}
+// Where two or more of three bits are set.
+__device__ __forceinline__ uint32_t majority(uint32_t x, uint32_t y, uint32_t z) {
+  return (x & y) | (x & z) | (y & z);
 }
 // Columns [lo, hi) as bits of word ww.
 __device__ __forceinline__ uint32_t col_bits(int ww, int lo, int hi) {
@@ -245,6 +255,7 @@ struct alignas(16) SmemIter {
   QIndex qmap[QR * QC];    // a block's index in s4, by position
   float wmin[kIterThreads / 64], wmax[kIterThreads / 64];
   float mn, nmin, thr;  // the region's smallest value, the noise there, the candidates' bound
+  float margin;         // of that bound; +inf where it does not apply
   unsigned int cnt, nopen, n2, fresh, unrep;
   unsigned int zones;  // bit 3 zy + zx: 3x3 zones of the tile (8 pixels along the edges) with a change
   int any_b1, live;
@@ -280,6 +291,12 @@ struct alignas(16) SmemIter {
     }
   }
 };
+
+// What 2c - min(u, d) - min(l, r) has to exceed for S > sigclip where the
+// noise is at least n (step 2).
+__device__ __forceinline__ float candidate_bound(float sigclip, float n, float margin) {
+  return (2.0f * sigclip) * n * (1.0f - 0x1p-14f) - margin;
+}
 
 // S (and N) at one region cell (2 or more inside the region).
 template <typename SM>
@@ -752,9 +769,10 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     const float nmin = noise_from_med<false>(fkey(mn), nc, f.rn2);  // no noise in the region is smaller
     const bool sane = nc.fast_sqrt && nc.gain >= 0x1p-30f && nc.gain <= 0x1p30f && sigclip >= 0x1p-30f &&
                       sigclip <= 0x1p30f && M <= 0x1p90f && mn <= M;
-    const float t = (2.0f * sigclip) * nmin * (1.0f - 0x1p-14f) - M * 0x1p-16f;
+    const float margin = M * 0x1p-16f, t = candidate_bound(sigclip, nmin, margin);
     if (tid == 0) {
       s.mn = mn;
+      s.margin = sane ? margin : __int_as_float(0x7f800000);
       s.nmin = nmin;
       s.thr = (sane && t > 0.0f) ? t : __int_as_float(0xff800000);
       if (!(M <= 0x1.fffffep127f)) atom_or(f.status, 1);
@@ -809,9 +827,143 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
         }
     }
   }
-  const unsigned int hbase = wave_reserve(&s.cnt, (unsigned int)__popc(hits));
+  unsigned int hbase = wave_reserve(&s.cnt, (unsigned int)__popc(hits));
   __syncthreads();
-  const unsigned int npc = s.cnt;
+  unsigned int npc = s.cnt;
+  // The smallest value says little where it is a dead pixel's or a border's:
+  // one zero pixel among 1e4 of a CMOS sky raises the hits of a tile from 77 to
+  // 950, and S at each costs a median.  So where the hits exceed the list, those
+  // whose median must reach a level v typical of the tile -- 13 of the window's
+  // 25 values do, or, separable, 3 values of 3 rows -- are held to the noise at
+  // v.  Any v is right; a median of largest minima of 16 x 2 pixels passes dead
+  // pixels, columns and borders by, and stars (950 -> 24 hits; 2050 -> 160 with
+  // a dead column every 64).  About 7000 cycles of a tile with three others on
+  // its CU, none on tiles without defects.  (6400 x 9600 uint16, 1e-3 of the
+  // pixels zero: 1.11 -> 0.66 ms, the sparse passes 0.71.  Small tiles have few
+  // pixels: their hits cost less than this.)
+  if (TW_ == 64 && __builtin_expect(npc > (unsigned int)ICAP && s.margin <= 0x1.fffffep127f, 0)) {  // (uniform)
+    // in the pool: a bit for each of the region's cells, the bit rows of the
+    // medians below v, and the values v is taken from
+    uint32_t* cells = reinterpret_cast<uint32_t*>(s.s4);
+    uint32_t* low_med = cells + RH * RW / 32 + 4;
+    float* levels = reinterpret_cast<float*>(low_med + RH * NW);
+    static_assert(RH * RW / 32 <= NT && RH * RW / 8 + 16 + RH * NW * 4 + 64 <= (int)sizeof(s.s4), "they fit");
+    float v = __int_as_float(0xff800000);
+#pragma unroll
+    for (int j = 0; j < PP; ++j) {
+      const float4 x = *reinterpret_cast<const float4*>(&s.c[prow(2 * j)][px0]);
+      const float4 y = *reinterpret_cast<const float4*>(&s.c[prow(2 * j) + 1][px0]);
+      float m = vmin3(vmin3(vmin3(x.x, x.y, x.z), x.w, y.x), vmin3(y.y, y.z, y.w), y.w);
+      m = vmin(m, dpp_move<0xb1, 0xf>(m));  // quad_perm 1, 0, 3, 2
+      m = vmin(m, dpp_move<0x4e, 0xf>(m));  // quad_perm 2, 3, 0, 1
+      v = vmax(v, m);
+    }
+    if ((tid & 63) >= PG * PRUNS) v = __int_as_float(0xff800000);  // (a quad of its own)
+    static_assert(PG * PRUNS == 60, "whole quads hold the region's columns");
+    v = vmax(v, __shfl_xor(v, 4));
+    v = vmax(v, __shfl_xor(v, 8));
+    if ((tid & 15) == 0) levels[tid >> 4] = v;
+    __syncthreads();
+    {  // the median of the 16
+      static_assert(NT == 256, "16 rows of lanes");
+      v = levels[tid & 15];
+      int rank = 0;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) rank += levels[j] < v || (levels[j] == v && j < (tid & 15)) ? 1 : 0;
+      const uint64_t at = __ballot(rank == 8);
+      v = __shfl(v, at ? __ffsll((long long)at) - 1 : 0);
+    }
+    const float t = candidate_bound(sigclip, noise_from_med<false>(fkey(v), nc, f.rn2), s.margin);
+    // (where it brings little, many hits stay too many)
+    if (t > (npc > 2u * ICAP ? 1.5f : 1.1f) * thr) {  // (uniform; false for a NaN)
+      if (tid == 0) s.cnt = 0u;
+      // [C < v] of the region's cells, one after another: 32 each thread, read
+      // from a different quarter row on in each lane (the banks)
+      if (tid < RH * RW / 32) {
+        uint32_t below = 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int part = (tid + j) & 7;
+          const float4 x = *reinterpret_cast<const float4*>(&s.c[0][0] + 32 * tid + 4 * part);
+          uint32_t n = sign_into(0u, x.w - v);
+          n = sign_into(n, x.z - v);
+          n = sign_into(n, x.y - v);
+          n = sign_into(n, x.x - v);
+          below |= n << (4 * part);
+        }
+        cells[tid] = below;
+      }
+      __syncthreads();
+      // which medians lie below v: a word of 32 pixels each thread, the counts bit-sliced
+      if (tid >= 4 * NW && tid < (RH - 4) * NW) {
+        uint32_t one[5], two[5], four[5];  // per row of the window: how many of its 5 cells lie below
+#pragma unroll
+        for (int a = 0; a < 5; ++a) {
+          const int i = (tid / NW - 2 + a) * RW + 32 * (tid % NW) - 2;
+          const uint32_t* p = cells + (i >> 5);
+          const uint32_t lo = __builtin_amdgcn_alignbit(p[1], p[0], i & 31);
+          const uint32_t hi = __builtin_amdgcn_alignbit(p[2], p[1], i & 31);
+          const uint32_t c1 = __builtin_amdgcn_alignbit(hi, lo, 1), c2 = __builtin_amdgcn_alignbit(hi, lo, 2);
+          const uint32_t c3 = __builtin_amdgcn_alignbit(hi, lo, 3), c4 = __builtin_amdgcn_alignbit(hi, lo, 4);
+          const uint32_t s1 = lo ^ c1 ^ c2, k1 = majority(lo, c1, c2), k2 = majority(s1, c3, c4);
+          one[a] = s1 ^ c3 ^ c4;
+          two[a] = k1 ^ k2;
+          four[a] = k1 & k2;
+        }
+        uint32_t low;  // medians below v
+        if (f.sepmed) {  // 3 rows with 3 cells below
+#pragma unroll
+          for (int a = 0; a < 5; ++a) one[a] = four[a] | (two[a] & one[a]);
+          const uint32_t s1 = one[0] ^ one[1] ^ one[2], k1 = majority(one[0], one[1], one[2]);
+          const uint32_t k2 = majority(s1, one[3], one[4]);
+          low = (k1 & k2) | ((k1 ^ k2) & (s1 ^ one[3] ^ one[4]));
+        } else {  // 13 cells below
+          const uint32_t o1 = one[0] ^ one[1] ^ one[2], p0 = majority(one[0], one[1], one[2]);
+          const uint32_t o = o1 ^ one[3] ^ one[4], p1 = majority(o1, one[3], one[4]);
+          const uint32_t t1 = two[0] ^ two[1] ^ two[2], q0 = majority(two[0], two[1], two[2]);
+          const uint32_t t2 = t1 ^ two[3] ^ two[4], q1 = majority(t1, two[3], two[4]);
+          const uint32_t w = t2 ^ p0 ^ p1, q2 = majority(t2, p0, p1);
+          const uint32_t f1 = four[0] ^ four[1] ^ four[2], e0 = majority(four[0], four[1], four[2]);
+          const uint32_t f2 = f1 ^ four[3] ^ four[4], e1 = majority(f1, four[3], four[4]);
+          const uint32_t f3 = q0 ^ q1 ^ q2, e2 = majority(q0, q1, q2);
+          const uint32_t r = f2 ^ f3, e3 = f2 & f3;  // o + 2 w + 4 r + 8 (e0 + e1 + e2 + e3) cells
+          const uint32_t x1 = e0 ^ e1 ^ e2, y1 = majority(e0, e1, e2);
+          const uint32_t x = x1 ^ e3, y = y1 | (x1 & e3);  // (at most 3 of them)
+          low = y | (x & r & (w | o));
+        }
+        low_med[tid] = low;
+      }
+      __syncthreads();
+      uint32_t keep = 0u;  // the lane's pixels over the bound at v, and those whose median is below it
+#pragma unroll
+      for (int j = 0; j < PP; ++j) {
+        const int y = prow(2 * j);
+        float4 up = *reinterpret_cast<const float4*>(&s.c[y - 1][px0]);
+        float4 cu = *reinterpret_cast<const float4*>(&s.c[y][px0]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const float4 dn = *reinterpret_cast<const float4*>(&s.c[y + k + 1][px0]);
+          const float l = dpp_move<0x138, 0xf>(cu.w), r = dpp_move<0x130, 0xf>(cu.x);
+          const float e0 = __builtin_fmaf(2.0f, cu.x, -(vmin(up.x, dn.x) + vmin(l, cu.y)));
+          const float e1 = __builtin_fmaf(2.0f, cu.y, -(vmin(up.y, dn.y) + vmin(cu.x, cu.z)));
+          const float e2 = __builtin_fmaf(2.0f, cu.z, -(vmin(up.z, dn.z) + vmin(cu.y, cu.w)));
+          const float e3 = __builtin_fmaf(2.0f, cu.w, -(vmin(up.w, dn.w) + vmin(cu.z, r)));
+          keep = keep + keep + (!(e0 <= t) ? 1u : 0u);
+          keep = keep + keep + (!(e1 <= t) ? 1u : 0u);
+          keep = keep + keep + (!(e2 <= t) ? 1u : 0u);
+          keep = keep + keep + (!(e3 <= t) ? 1u : 0u);
+          const uint32_t low = low_med[(y + k) * NW + (px0 >> 5)] >> (px0 & 31);
+          keep |= __brev(low) >> 28;
+          up = cu;
+          cu = dn;
+        }
+      }
+      hits &= keep;
+      hbase = wave_reserve(&s.cnt, (unsigned int)__popc(hits));
+      __syncthreads();
+      npc = s.cnt;
+    }
+  }
   uint2* open = reinterpret_cast<uint2*>(s.s4);  // candidates and their med7 bounds, before the pool's use
   constexpr int OCAP = (int)(sizeof(s.s4) / sizeof(uint2));
   for (unsigned int c0 = 0; c0 < npc; c0 += ICAP) {  // one round unless the tile is dense

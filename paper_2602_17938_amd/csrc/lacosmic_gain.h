@@ -218,7 +218,9 @@ __device__ __forceinline__ void gain_windows(GainWork* g, uint32_t key) {
 }
 
 // The near histogram: one bin for each key from GainWork::near0 on, in the S
-// plane, which an estimating frame's iteration rewrites after its estimate.
+// plane.  Nothing is kept there over an estimate: the passes of an estimating
+// frame's iteration rewrite S everywhere after it, the one-launch iteration
+// stores there what it reads itself, and each estimate clears the bins first.
 constexpr int kGainNear = 16384;
 // Frames of fewer pixels select instead: their passes are all latency, and the
 // search of the near histogram takes as long as the two passes it saves (about

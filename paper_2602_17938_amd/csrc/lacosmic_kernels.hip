@@ -120,13 +120,14 @@ __global__ __launch_bounds__(kIterThreads, kIterWaves) void k_iter(const FrameDe
   // those atomics, 165 against 100 us for iteration 1 of a 4000 x 6500 frame.)
   const unsigned long long news = !listed && it > 0 && f.early_stop ? ldg(f.n_new, it - 1) : 1ull;
   if (f.est_gain && news == 0ull) return;
-  // the lists alternate between two planes no one-launch iteration uses
-  const IterList next{reinterpret_cast<int*>((it & 1) ? f.splane : f.sp), f.counts + it + 1, 0};
+  // the lists alternate between two bit planes that this form has no use for
+  // (each has room for a word per tile of either shape)
+  const IterList next{reinterpret_cast<int*>((it & 1) ? f.g1 : f.g2), f.counts + it + 1, 0};
   if (!listed) {  // (every tile is due)
     tile_iter<TH, TW_>(f, it, xcd_remap(blockIdx.x, gridDim.x), next, news, s);
     return;
   }
-  const int* list = reinterpret_cast<const int*>((it & 1) ? f.sp : f.splane);
+  const int* list = reinterpret_cast<const int*>((it & 1) ? f.g2 : f.g1);
   int t = ldg(list, blockIdx.x);  // (a list has room for every tile; read with its length, not after it)
   const unsigned int n = ldg(f.counts, it);
 #pragma unroll 1

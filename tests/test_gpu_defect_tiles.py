@@ -1,7 +1,8 @@
 """GPU tests of the one-launch iterations on frames with defects: dead pixels,
 bad columns, borders and sentinels far below the sky, where the smallest value
 of a tile's region says nothing about its noise and candidates are held to a
-local bound instead.  Bit for bit against the CPU oracle around both tile
+local bound instead; and on dense frames, whose tiles exceed the LDS pool and
+list (noise taken for candidates, many cosmic rays).  Bit for bit against the CPU oracle around both tile
 shapes, and on large frames no slower than the sparse passes, the general form
 (LACOSMIC_FUSED_MAX_PX=0), which do the same work whatever the pixels."""
 
@@ -35,13 +36,14 @@ def _spoil(img, how):
     return img
 
 
-def _check(img, gain, rn, sigclip=4.5, sepmed=False, u16=False, niter=4):
+def _check(img, gain, rn, sigclip=4.5, sepmed=False, u16=False, niter=4, est=False):
     import oracle
     import torch
     L = lac()
-    r = oracle.lacosmic(img, gain, rn, sigclip, 0.3, 5.0, niter, nthreads=host_threads(), sepmed=sepmed)
+    r = oracle.lacosmic(img, gain, rn, sigclip, 0.3, 5.0, niter, nthreads=host_threads(), sepmed=sepmed,
+                        estimate_gain=est)
     d = torch.from_numpy(img.astype(np.uint16)).cuda() if u16 else to_dev(img)
-    m, c, st = L.run_ex(d, L.make_params(gain, rn, sigclip, 0.3, 5.0, niter, sepmed=sepmed))
+    m, c, st = L.run_ex(d, L.make_params(gain, rn, sigclip, 0.3, 5.0, niter, sepmed=sepmed, estimate_gain=est))
     assert_bits_equal(m.cpu().numpy(), r["mask"], "mask")
     assert_bits_equal(c.cpu().numpy(), r["clean"], "clean")
     assert [st.n_new[k] for k in range(niter)] == list(r["n_new"])
@@ -69,6 +71,59 @@ def test_defects_without_read_noise(how, sepmed, shape):
     from paper_2602_17938_amd import synth
     img = _spoil(synth.make_frame("ccd", *shape, seed=6), how)
     _check(img, 1.0, 0.0, sepmed=sepmed)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("case", ["rays", "more rays", "background", "sepmed", "faint", "all", "gain", "estimated",
+                                  "negative"])
+def test_dense_tiles_match_the_oracle(case, shape):
+    """From blocks of S that just exceed the pool (rays) to every pixel of a
+    tile evaluated (all)."""
+    from paper_2602_17938_amd import synth
+    sky = lambda scale=1.0: synth.make_frame("ccd", *shape, seed=8, cr_scale=scale)
+    if case == "rays":
+        _check(sky(15.0), 1.0, 5.0)
+    elif case == "more rays":
+        _check(sky(120.0), 1.0, 5.0)
+    elif case in ("background", "sepmed"):  # subtracted: the noise model holds the read noise only
+        _check((sky() - F32(200.0)).astype(F32), 1.0, 5.0, sepmed=case == "sepmed")
+    elif case == "faint":
+        _check(sky(), 1.0, 5.0, sigclip=1.0)
+    elif case == "all":
+        _check(sky(), 1.0, 5.0, sigclip=1e-3, niter=2)
+    elif case == "gain":  # five times too large
+        p = synth.params_for("cmos")
+        _check(synth.make_frame("cmos", *shape, seed=4), 5 * p.gain, p.readnoise, u16=True)
+    elif case == "estimated":  # (the estimate's bins lie in the plane that holds a dense tile's S)
+        _check(sky(30.0), 0.0, 5.0, sigclip=1.5, est=True, niter=3)
+    else:
+        _check((sky() * F32(-1.0)).astype(F32), 1.0, 5.0, sigclip=2.0)
+
+
+def test_dense_frames_in_a_batch():
+    from paper_2602_17938_amd import synth
+    L = lac()
+    imgs = [synth.make_frame("ccd", 700, 811, seed=3), synth.make_frame("ccd", 900, 640, seed=4, cr_scale=60.0)]
+    imgs.append((imgs[0][:500] - F32(200.0)).astype(F32))
+    masks, cleans = L.run_batch([to_dev(x) for x in imgs], L.make_params(1.0, 5.0, 2.0, 0.3, 5.0, 4))
+    for i, img in enumerate(imgs):
+        import oracle
+        r = oracle.lacosmic(img, 1.0, 5.0, 2.0, 0.3, 5.0, 4, nthreads=host_threads())
+        assert_bits_equal(masks[i].cpu().numpy(), r["mask"], "mask %d" % i)
+        assert_bits_equal(cleans[i].cpu().numpy(), r["clean"], "clean %d" % i)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_nonfinite_pixels_in_dense_tiles(shape):
+    from paper_2602_17938_amd import synth
+    L = lac()
+    img = (synth.make_frame("ccd", *shape, seed=8) - F32(200.0)).astype(F32)
+    for bad in (np.nan, np.inf, -np.inf):
+        x = img.copy()
+        x[shape[0] // 2, shape[1] // 3] = bad
+        with pytest.raises(L.LacosmicError) as e:
+            L.run_ex(to_dev(x), L.make_params(1.0, 5.0, 0.5))
+        assert e.value.status == L.ENONFINITE
 
 
 def _ms(call):
@@ -126,3 +181,16 @@ def test_defects_do_not_slow_the_tiles(kind, how, rn, monkeypatch):
     p = synth.params_for(kind)
     ratio = _tiles_against_passes(_large(kind, how), p.gain, p.readnoise if rn is None else rn, 4.5, monkeypatch)
     assert ratio < LIMIT
+
+
+@pytest.mark.parametrize("kind,sigclip,sky", [("ccd", 4.5, 200.0), ("cmos", 4.5, 200.0), ("ccd", 2.0, 0.0),
+                                              ("ccd", 1.0, 0.0), ("cmos", 1.0, 0.0)])
+def test_dense_frames_do_not_slow_the_tiles(kind, sigclip, sky, monkeypatch):
+    """A background (sky) subtracted, or a low detection limit."""
+    import torch
+    from paper_2602_17938_amd import synth
+    p = synth.params_for(kind)
+    x = _large(kind, "none")
+    if sky:
+        x = x.to(torch.int32).to(torch.float32) - sky if kind == "cmos" else x - sky
+    assert _tiles_against_passes(x, p.gain, p.readnoise, sigclip, monkeypatch) < LIMIT

@@ -1,5 +1,5 @@
 // Batched path: many frames of mixed sizes together, in one of two forms.
-// Batches of at most kIterBatchPx pixels run one launch per iteration over the
+// Batches of at most kIterPx pixels run one launch per iteration over the
 // tiles of all frames (lacosmic_iter.h).  Larger ones run one launch per pass,
 // the whole niter loop recorded once per batch shape as a HIP graph and
 // replayed; tile shape, launch form and group count are picked by timing the
@@ -25,14 +25,6 @@ namespace lac {
 static size_t counter_stride(int niter) {
   return (size_t)niter + 2 + ((size_t)kCntPerIter * niter + 1) / 2;
 }
-
-// Pixels up to which a batch runs one launch per iteration.  The passes'
-// chain of about seven launches per iteration costs about 0.6 ms whatever the
-// batch (four iterations); per pixel it is the cheaper form, its sparse passes
-// running on full waves over all frames' lists.  Measured, tiles against
-// passes: 9.3 Mpx of cutouts 0.56 / 0.94 ms, 35 Mpx 0.56 / 0.78, 67 Mpx 0.92 /
-// 1.10, 100 Mpx 1.28 / 1.40, 1028 Mpx 11.3 / 8.5.
-constexpr int64_t kIterBatchPx = int64_t(1) << 27;
 
 // Frames are split into groups of about equal pixel counts; each group's
 // passes form their own chain of launches, on its own stream inside the
@@ -569,7 +561,7 @@ extern "C" int lacosmic_run_batch(int32_t n, const float* const* imgs, const int
       BatchPlan* P = nullptr;
       int64_t pixels = 0;
       for (int i = 0; i < n; ++i) pixels += hs[i] * ws[i];
-      if (pixels <= kIterBatchPx && !std::getenv("LACOSMIC_BATCH_PLAN")) {
+      if (pixels <= kIterPx && !std::getenv("LACOSMIC_BATCH_PLAN")) {
         P = new BatchPlan();
         const int rc = build_plan(*P, n, hs, ws, niter, early, est, c->cfg, kModeGrid,
                                   std::max(1, pinned_groups()), true, c->stream);

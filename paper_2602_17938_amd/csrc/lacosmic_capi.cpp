@@ -58,7 +58,7 @@ static bool finite_pos(float v) { return std::isfinite(v) && v > 0.0f; }
 int fused_form(int64_t h, int64_t w, const lacosmic_params& p, bool caller_ws) {
   if (p.flags & LACOSMIC_F_FULL_SP) return kFusedOff;
   const char* env = std::getenv("LACOSMIC_FUSED_MAX_PX");
-  const int64_t limit = env ? std::atoll(env) : caller_ws ? kFusedMaxPx : kMaxPixels;
+  const int64_t limit = env ? std::atoll(env) : caller_ws ? kFusedMaxPx : kIterPx;
   if (h * w > limit) return kFusedOff;
   return caller_ws ? kFusedPingPong : kFusedTiles;
 }

@@ -57,11 +57,23 @@ struct BatchCache;
 // Single-frame runs of at most this many pixels are one launch per iteration
 // (LACOSMIC_FUSED_MAX_PX overrides; 0 turns it off), those with the full-S'
 // flag never.  A run whose workspace the caller cannot look into leaves no S
-// or candidate plane behind and takes the launches of lacosmic_iter.h at any
-// size; one in a caller's workspace leaves them there, which one launch per
-// iteration does faster than the sparse passes only for small frames
-// (crossover measured between 512^2 and 1024^2).
+// or candidate plane behind and takes the launches of lacosmic_iter.h up to
+// kIterPx pixels; one in a caller's workspace leaves them there, which one
+// launch per iteration does faster than the sparse passes only for small
+// frames (crossover measured between 512^2 and 1024^2).
 constexpr int64_t kFusedMaxPx = int64_t(1) << 19;
+// Pixels of a frame, or of a batch, up to which it runs one launch per
+// iteration over its tiles.  The passes' chain of about seven launches per
+// iteration costs about 0.5 ms whatever the size (four iterations); per pixel
+// it is the cheaper form, its sparse passes running on full waves over all
+// tiles' lists, and dead pixels cost it nothing.  Passes / tiles in ms, with
+// none, 1e-4 and 1e-3 of the pixels zero: a 134 Mpx frame 1.80 / 1.31, 1.80 /
+// 1.54, 1.92 / 1.82; 268 Mpx 2.90 / 2.53, 2.90 / 2.93, 3.03 / 3.50; 576 Mpx
+// 5.69 / 5.30, 5.82 / 6.17, 6.23 / 7.40.  Batches of 2048^2 frames, 67 Mpx
+// 1.05 / 0.81, 1.06 / 0.91, 1.09 / 1.06; 130 Mpx 1.72 / 1.44, 1.72 / 1.63,
+// 1.79 / 1.93; of 500^2 frames, 125 Mpx 3.06 / 2.13, 3.07 / 2.40, 3.16 / 2.85;
+// the 64 mixed frames, 1028 Mpx, 8.5 / 11.3.
+constexpr int64_t kIterPx = int64_t(1) << 27;
 int fused_form(int64_t h, int64_t w, const lacosmic_params& p, bool caller_ws);
 
 // A recorded single-frame run (counter reset and every iteration's launches)

@@ -158,12 +158,12 @@ def _tiles_against_passes(img, gain, rn, sigclip, monkeypatch):
     return tiles / passes
 
 
-def _large(kind, how):
-    """16 copies of a spoilt frame side by side, as the camera delivers it."""
+def _large(kind, how, copies=4):
+    """Copies of a spoilt frame side by side, as the camera delivers it."""
     import torch
     from paper_2602_17938_amd import synth
     shape = (1024, 1024) if kind == "ccd" else (1600, 2400)
-    x = torch.from_numpy(_spoil(synth.make_frame(kind, *shape, seed=9), how)).cuda().repeat(4, 4)
+    x = torch.from_numpy(_spoil(synth.make_frame(kind, *shape, seed=9), how)).cuda().repeat(copies, copies)
     return x.to(torch.int32).to(torch.uint16) if kind == "cmos" else x.contiguous()
 
 
@@ -194,3 +194,13 @@ def test_dense_frames_do_not_slow_the_tiles(kind, sigclip, sky, monkeypatch):
     if sky:
         x = x.to(torch.int32).to(torch.float32) - sky if kind == "cmos" else x - sky
     assert _tiles_against_passes(x, p.gain, p.readnoise, sigclip, monkeypatch) < LIMIT
+
+
+def test_defects_do_not_slow_the_largest_frames(monkeypatch):
+    """Far above the size up to which frames run on tiles, whose time per pixel
+    grows with the defects where the passes' does not."""
+    from paper_2602_17938_amd import synth
+    p = synth.params_for("cmos")
+    x = _large("cmos", "dead1e-3", 12)  # 553 Mpx
+    assert _tiles_against_passes(x, p.gain, p.readnoise, 4.5, monkeypatch) < 1.15
+    lac().shutdown()  # (its workspace: 9 GB)

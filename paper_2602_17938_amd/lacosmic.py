@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import contextlib
 import ctypes
+import itertools
 import os
 import re
 
@@ -278,21 +279,22 @@ def run_batch(imgs, params, out_masks=None, out_cleans=None, stream="current"):
     or a list.  Returns lists of masks and cleans."""
     n = len(imgs)
     imgs = [_dev_image(x, allow_u16=True) for x in imgs]
-    if isinstance(params, Params):
-        params = [params] * n
+    # (any iterable of parameters or outputs, read once)
+    params = [params] * n if isinstance(params, Params) else list(itertools.islice(params, n))
     if out_masks is None:
         out_masks = [torch.empty(x.shape, dtype=torch.uint8, device=x.device) for x in imgs]
     if out_cleans is None:
         out_cleans = [torch.empty(x.shape, dtype=torch.float32, device=x.device) for x in imgs]
     # one array of each kind, filled in bulk
     def addresses(ts):
-        if len(ts) > n:
+        at = [t.data_ptr() for t in ts]
+        if len(at) > n:
             raise IndexError("more outputs than images")
-        return [t.data_ptr() for t in ts] + [0] * (n - len(ts))
+        return at + [0] * (n - len(at))
 
     ptrs = np.array(addresses(imgs) + addresses(out_masks) + addresses(out_cleans), np.uint64)
     dims = np.array([x.shape for x in imgs], np.int64).reshape(n, 2).T.copy()
-    a_p = (Params * n)(*params[:n])  # copies: the callers' parameters stay as they are
+    a_p = (Params * n)(*params)  # copies: the callers' parameters stay as they are
     for q, x in zip(a_p, imgs):
         if x.dtype == torch.uint16:
             q.flags |= F_INPUT_U16

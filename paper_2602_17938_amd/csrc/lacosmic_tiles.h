@@ -624,50 +624,6 @@ __device__ __forceinline__ float sprime_at(const FrameDev& f, int gy, int gx) {
   return s[12] - funkey(med25_of(v, f.sepmed));
 }
 
-// med3 at the 7x7 positions around the centre of a 9x9 patch of keys.
-__device__ __forceinline__ void objlim_med3(const int* p, int* v49, int sep) {
-  if (sep) {  // separable: the row medians of 3, then their column medians
-#pragma unroll
-    for (int a = 0; a < 7; ++a)
-#pragma unroll
-      for (int b = 0; b < 7; ++b) {
-        const int* q = p + a * 9 + b;
-        v49[a * 7 + b] = kmed3(kmed3(q[0], q[1], q[2]), kmed3(q[9], q[10], q[11]),
-                               kmed3(q[18], q[19], q[20]));
-      }
-  } else {
-    // med3 of every 3x3 window of the patch from its three sorted columns:
-    // the median of 9 is med3(max of the column minima, med3 of the column
-    // medians, min of the column maxima).  Row a of the patch is last used
-    // by output row a.
-#pragma unroll
-    for (int a = 0; a < 7; ++a) {
-      int lo[9], md[9], hi[9];
-#pragma unroll
-      for (int b = 0; b < 9; ++b) {
-        const int x0 = p[a * 9 + b], x1 = p[(a + 1) * 9 + b], x2 = p[(a + 2) * 9 + b];
-        lo[b] = kmin3(x0, x1, x2);
-        md[b] = kmed3(x0, x1, x2);
-        hi[b] = kmax3(x0, x1, x2);
-      }
-#pragma unroll
-      for (int b = 0; b < 7; ++b)
-        v49[a * 7 + b] = kmed3(kmax3(lo[b], lo[b + 1], lo[b + 2]),
-                               kmed3(md[b], md[b + 1], md[b + 2]),
-                               kmin3(hi[b], hi[b + 1], hi[b + 2]));
-    }
-  }
-}
-// Step 5's decision from med3 around the pixel (v49) and its noise N.
-__device__ __forceinline__ bool objlim_decide(const int* v49, const FrameDev& f, float N, float spv) {
-  const float m3 = funkey(v49[24]);
-  const float m7 = funkey(med49_of(v49, f.sepmed));
-  const float F = m3 - m7;
-  const float fr = F / N;
-  const float fn = (fr > 0.01f) ? fr : 0.01f;
-  return (spv / fn) > f.objlim;
-}
-
 // Step 5 at one candidate pixel (gy, gx): fine structure F = med3 - med7(med3)
 // (med7 clamps on med3's own grid), f = F / N floored at 0.01; returns
 // whether S' / f exceeds objlim.  Reads C from global memory.  Away from the
@@ -695,7 +651,37 @@ __device__ __forceinline__ bool objlim_test(const FrameDev& f, const NoiseCoef& 
         for (int b = 0; b < 5; ++b) v25[a * 5 + b] = p[(a + 2) * 9 + (b + 2)];
       N = noise_from_med(med25_of(v25, f.sepmed), nc, f.rn2);
     }
-    objlim_med3(p, v49, f.sepmed);
+    if (f.sepmed) {  // separable: the row medians of 3, then their column medians
+#pragma unroll
+      for (int a = 0; a < 7; ++a)
+#pragma unroll
+        for (int b = 0; b < 7; ++b) {
+          const int* q = p + a * 9 + b;
+          v49[a * 7 + b] = kmed3(kmed3(q[0], q[1], q[2]), kmed3(q[9], q[10], q[11]),
+                                 kmed3(q[18], q[19], q[20]));
+        }
+    } else {
+      // med3 of every 3x3 window of the patch from its three sorted columns:
+      // the median of 9 is med3(max of the column minima, med3 of the column
+      // medians, min of the column maxima).  Row a of the patch is last used
+      // by output row a.
+#pragma unroll
+      for (int a = 0; a < 7; ++a) {
+        int lo[9], md[9], hi[9];
+#pragma unroll
+        for (int b = 0; b < 9; ++b) {
+          const int x0 = p[a * 9 + b], x1 = p[(a + 1) * 9 + b], x2 = p[(a + 2) * 9 + b];
+          lo[b] = kmin3(x0, x1, x2);
+          md[b] = kmed3(x0, x1, x2);
+          hi[b] = kmax3(x0, x1, x2);
+        }
+#pragma unroll
+        for (int b = 0; b < 7; ++b)
+          v49[a * 7 + b] = kmed3(kmax3(lo[b], lo[b + 1], lo[b + 2]),
+                                 kmed3(md[b], md[b + 1], md[b + 2]),
+                                 kmin3(hi[b], hi[b + 1], hi[b + 2]));
+      }
+    }
   } else {
     int v25[25];
 #pragma unroll
@@ -722,7 +708,12 @@ __device__ __forceinline__ bool objlim_test(const FrameDev& f, const NoiseCoef& 
       }
     }
   }
-  return objlim_decide(v49, f, N, spv);
+  const float m3 = funkey(v49[24]);
+  const float m7 = funkey(med49_of(v49, f.sepmed));
+  const float F = m3 - m7;
+  const float fr = F / N;
+  const float fn = (fr > 0.01f) ? fr : 0.01f;
+  return (spv / fn) > f.objlim;
 }
 
 

@@ -216,8 +216,7 @@ DevCtx* ctx_for(int dev) {
 }
 
 hipStream_t DevCtx::stream_after_null() {
-  // (always by the event: a query of the null stream is a snapshot on the host
-  // and orders nothing on the device)
+  if (hipStreamQuery(nullptr) == hipSuccess) return stream;  // nothing to wait for
   if (hipEventRecord(null_done, nullptr) != hipSuccess ||
       hipStreamWaitEvent(stream, null_done, 0) != hipSuccess)
     return nullptr;

@@ -292,7 +292,8 @@ int lacosmic_set_tile_shape(int32_t cfg);
  * tile and 8 pixels around it in LDS (one iteration reads them within 8
  * pixels): in the library's own workspace or its static scratch up to 2^27
  * pixels; in a caller's workspace, where the launch also leaves the planes
- * described above, up to 2^19 pixels (larger frames run the sparse passes).
+ * described above, up to 2^19 pixels and without LACOSMIC_F_ESTIMATE_GAIN
+ * (other frames run the sparse passes).
  * LACOSMIC_FUSED_MAX_PX, read at each call, overrides both limits; 0 turns it
  * off.  Results are identical either way. */
 

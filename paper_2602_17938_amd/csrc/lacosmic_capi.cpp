@@ -60,6 +60,11 @@ int fused_form(int64_t h, int64_t w, const lacosmic_params& p, bool caller_ws) {
   const char* env = std::getenv("LACOSMIC_FUSED_MAX_PX");
   const int64_t limit = env ? std::atoll(env) : caller_ws ? kFusedMaxPx : kIterPx;
   if (h * w > limit) return kFusedOff;
+  // With the image in two places in turn, the gain estimate chose between them
+  // per iteration.  Compiled for gfx950 that choice loaded the address from
+  // address 0 in every second iteration from the last (k_gain<0>; k_gain<1>
+  // took the input) and faulted: estimating frames run the passes there.
+  if (caller_ws && (p.flags & LACOSMIC_F_ESTIMATE_GAIN)) return kFusedOff;
   return caller_ws ? kFusedPingPong : kFusedTiles;
 }
 

@@ -74,18 +74,15 @@ __device__ __forceinline__ unsigned long long gain_atomic_load(const unsigned lo
 }
 
 // The current image: the input in iteration 0 (float32 or uint16), the
-// cleaned image after that -- which the launches of kFusedPingPong keep
-// alternately in the output image and the workspace's first list plane, the
-// previous iteration's output holding it.  Pixels are taken canonical (-0 as
-// +0).
+// cleaned image after that.  (The launches of kFusedPingPong keep it in two
+// places in turn: frames that estimate their gain do not run them.)  Pixels are
+// taken canonical (-0 as +0).
 struct GainImage {
   const float* f32;
   const uint16_t* u16;  // instead, if not null
   __device__ __forceinline__ GainImage(const FrameDev& f, int it) {
     u16 = it == 0 ? f.img16 : nullptr;
-    f32 = it == 0 ? f.img
-          : (f.fused != kFusedPingPong || ((f.niter - it) & 1) == 0) ? f.clean
-                                                                     : reinterpret_cast<const float*>(f.list);
+    f32 = it == 0 ? f.img : f.clean;
   }
   __device__ __forceinline__ float at(int64_t i) const {
     return u16 ? (float)ldg(u16, i) : ldg(f32, i) + 0.0f;

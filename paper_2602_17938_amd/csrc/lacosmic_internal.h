@@ -60,7 +60,8 @@ struct BatchCache;
 // or candidate plane behind and takes the launches of lacosmic_iter.h up to
 // kIterPx pixels; one in a caller's workspace leaves them there, which one
 // launch per iteration does faster than the sparse passes only for small
-// frames (crossover measured between 512^2 and 1024^2).
+// frames (crossover measured between 512^2 and 1024^2).  (Estimating frames
+// run the passes there: fused_form.)
 constexpr int64_t kFusedMaxPx = int64_t(1) << 19;
 // Pixels of a frame, or of a batch, up to which it runs one launch per
 // iteration over its tiles.  The passes' chain of about seven launches per

@@ -58,7 +58,7 @@ struct SmemFused {
 
 // The image iteration it writes (iteration it + 1 reads it): C ping-pongs
 // between the output image and the workspace's first list plane, ending in
-// the output (the gain estimate reads it the same way).
+// the output.
 __device__ __forceinline__ float* fused_dst(const FrameDev& f, int it) {
   return ((f.niter - 1 - it) & 1) == 0 ? f.clean : reinterpret_cast<float*>(f.list);
 }

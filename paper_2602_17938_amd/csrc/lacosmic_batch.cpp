@@ -607,11 +607,13 @@ extern "C" int lacosmic_batch_pass_ms(float* ms, int32_t n, void* hip_stream) {
     if (!c->batch || !c->batch->plan) return 0;
     BatchPlan& P = *c->batch->plan;
     hipStream_t s = hip_stream ? static_cast<hipStream_t>(hip_stream) : c->stream_after_null();
-    if (P.marks.empty()) {
-      P.marks.resize((size_t)P.ngroups * (kPassesPerIter * P.niter + 1), nullptr);
-      for (auto& ev : P.marks)
-        if (hipEventCreate(&ev) != hipSuccess) return LACOSMIC_EHIP;
-    }
+    // (those a failed call did not get to are created by the next)
+    P.marks.resize((size_t)P.ngroups * (kPassesPerIter * P.niter + 1), nullptr);
+    for (auto& ev : P.marks)
+      if (!ev && hipEventCreate(&ev) != hipSuccess) {
+        ev = nullptr;
+        return LACOSMIC_EHIP;
+      }
     if (!s || hipStreamWaitEvent(s, P.run_done, 0) != hipSuccess ||
         enqueue_plan(P, s, true) != hipSuccess || hipEventRecord(P.run_done, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)

@@ -1446,9 +1446,10 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       stg(iter_stamp(f, 1), tile, 0u);
     }
   }
-  if (it > 0 && it + 1 < f.niter && tid < 9) {
+  if (it > 0 && it + 1 < f.niter && !f.est_gain && tid < 9) {
     // the tiles whose region holds a change: this one, and those beside a
-    // zone along its edge that holds one
+    // zone along its edge that holds one (a frame that estimates its gain runs
+    // all its tiles)
     const uint32_t zr = tid < 3 ? 0x007u : tid < 6 ? 0x1ffu : 0x1c0u;
     const uint32_t zc = tid % 3 == 0 ? 0x049u : tid % 3 == 1 ? 0x1ffu : 0x124u;
     const int n = grid.neighbour(ty, tx, tid);

@@ -282,9 +282,10 @@ int lacosmic_server_destroy(lacosmic_server* s);
  * pixels per tile.  Returns LACOSMIC_EINVAL past the last one.  Results never
  * depend on the tile shape; only speed does. */
 int lacosmic_get_tile_shape(int32_t cfg, int32_t* th, int32_t* tw);
-/* Select the tile shape of the single-frame path on the current device (the
+/* Select the tile shape of the single-frame passes on the current device (the
  * autotuner's hook; the LACOSMIC_TILE_CFG environment variable sets the
- * initial choice). */
+ * initial choice).  Single-frame runs that take one launch per iteration, as
+ * described below, have tiles of their own. */
 int lacosmic_set_tile_shape(int32_t cfg);
 
 /* Single-frame runs without LACOSMIC_F_FULL_SP run each iteration as one
@@ -305,9 +306,10 @@ int lacosmic_set_tile_shape(int32_t cfg);
  * the call stores in the workspace, so one graph serves every call of that
  * key; at most 8 are kept per device) and replays the counter reset and every
  * launch of the run.  Results are identical either way.  On MI355X the eager
- * launches take less time per run (512 x 512: 0.148 against 0.159 ms per
- * isolated call, 4096 x 4096: 0.456 against 0.465 ms); the graph saves the
- * host the launches, for callers whose thread is the limit. */
+ * launches take less time per run (512 x 512: 0.073 against 0.086 ms per
+ * isolated call, 4096 x 4096: 0.262 against 0.276 ms; in a caller's workspace
+ * 0.153 / 0.166 and 0.435 / 0.450); the graph saves the host the launches, for
+ * callers whose thread is the limit. */
 int lacosmic_set_frame_graphs(int32_t on);
 
 /* Self-check of the square root the noise model uses when a frame's noise

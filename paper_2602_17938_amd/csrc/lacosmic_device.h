@@ -73,13 +73,17 @@ constexpr int kFusedTiles = 2;     // one launch per iteration, results only (la
 // pixel (y, 64 j + i); rows are wpr words long; bits past the frame's last
 // column are zero.
 struct FrameDev {
-  const float* img;            // input, ADU, h*w (read in iteration 0 only)
+  const float* img;            // input, ADU, h*w (read in iteration 0; by kFusedTiles in each)
   const uint16_t* img16;       // the input as uint16 ADU instead (then img is unused), or null
-  float* clean;                // current image C; iteration 0 writes all of it
+  float* clean;                // current image C; iteration 0 writes all of it (kFusedTiles
+                               // writes it and reads it in the gain estimate only,
+                               // kFusedPingPong keeps C here and in list in turn)
   float* splane;               // S, h*w: all of it in iteration 0, then kept up to date
+                               // (kFusedTiles: S of dense tiles, during a launch)
   float* sp;                   // S' at the candidates (every pixel with full_sp), h*w
   uint64_t* g1;                // S' > sigclip (exact at the candidates)
   uint64_t* g2;                // S' > sigfrac * sigclip (exact where growth can reach)
+                               // (kFusedTiles: tile lists, in both in turn)
   uint64_t* b1;                // candidates passing steps 4-5
                                // (the three kept across iterations outside R4)
   uint64_t* cb;                // candidates S > sigclip, kept up to date with S

@@ -1,8 +1,9 @@
 // One whole iteration of a frame in one launch, for runs whose workspace no
 // caller can look into (the library's cached one, the static scratch, a
-// batch, the server): only the mask and the cleaned image are results there,
-// so S, S' and the candidate planes need not exist, and nothing is computed
-// where a bound already decides.
+// batch's): only the mask and the cleaned image are results there, so S, S' and
+// the candidate planes need not exist, and nothing is computed where a bound
+// already decides.  (The server's steps share launches between frames at
+// different iterations and run the passes.)
 //
 // One block per tile of TH x TW output pixels.  One iteration reads the
 // previous image and mask within 8 pixels of an output pixel (replacement 2,

@@ -64,7 +64,9 @@ inline bool pass_runs(int pass, int it, int niter, bool est = false) {
 
 // Tile shapes of the one-launch iterations (lacosmic_iter.h): 32 x 32 output
 // pixels for runs of at most kIterSmallPx pixels in all, whose 64 x 64 tiles
-// would leave CUs idle, else 64 x 64.
+// would leave CUs idle, else 64 x 64.  The two were measured equal between
+// 1.1 and 2 Mpx (1100 x 1000 116 against 127 us, 1400^2 131 against 125), so
+// the line lies on the low side.
 constexpr int kIterSmall = 0, kIterLarge = 1;
 constexpr int64_t kIterSmallPx = int64_t(1) << 20;
 int iter_shape(int64_t pixels);

@@ -10,8 +10,9 @@
 // never passes the array's name to a kernel (on the host it is only a
 // stand-in), only the resolved address.  Every call on a device shares that
 // device's array and leaves its contents behind: the launches clear what must
-// start at zero (counters, list lengths, strip stamps, status; the per-
-// iteration bit planes are rewritten by the passes that own them), so calls
+// start at zero (counters, list lengths, status, and for the passes the strip
+// stamps; the tiles' state words and stamps are written by iteration 0, bit
+// planes by the launches that own them), so calls
 // in sequence are independent, but calls that overlap on one device race.
 #include <hip/hip_runtime.h>
 

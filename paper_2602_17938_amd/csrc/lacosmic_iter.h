@@ -1109,8 +1109,9 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     const unsigned int nq = (unsigned int)__builtin_amdgcn_readlane(upto, 63);
     // Where the pool does not hold them (a dense tile), S is kept in the frame's
     // S plane, which holds nothing else meanwhile -- tiles beside this one store
-    // the same values there -- and the pool's place has the list.
-    const bool big = nq > (unsigned int)QCAP;
+    // the same values there -- and the pool's place has the list.  (A small
+    // tile's pool holds every block.)
+    const bool big = QCAP < QR * QC && nq > (unsigned int)QCAP;
     uint16_t* list = big ? reinterpret_cast<uint16_t*>(s.s4) : s.lst;
     const unsigned int cap = big ? sizeof(s.s4) / 2 : ICAP;
     // S at the pixels of block j's part: PX of its pixels, in each of 4 / PX

@@ -1188,7 +1188,10 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     __syncthreads();
     next_phase();
     const unsigned int n2 = s.n2;
-    if (n2 > cap) return false;
+    if (n2 > cap) {
+      __syncthreads();  // (every wave has read the count before it is cleared)
+      return false;
+    }
     evaluate(list, n2, [&](int r, int q, int* v) __attribute__((always_inline)) {
       if (big)
         iter_plane_window(f, ry0 + r, rx0 + q, v);

@@ -100,6 +100,31 @@ def test_dense_tiles_match_the_oracle(case, shape):
         _check((sky() * F32(-1.0)).astype(F32), 1.0, 5.0, sigclip=2.0)
 
 
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("side,step", [(26, 1), (56, 3)])
+def test_more_pixels_to_evaluate_than_the_list_holds(side, step, shape):
+    """Bright pixels and a sigfrac so small that nearly every pixel beside one is
+    evaluated, on 64 x 64 tiles more of them than the list holds while the
+    candidates still fit it: 26 x 26 pixels side by side (390 candidates, 256
+    blocks: all the pool holds, 536 pixels of 512), and every third of 56 x 56
+    (380, 1296, 2358 pixels of 2048)."""
+    import oracle
+    L = lac()
+    h, w = shape
+    g = np.random.Generator(np.random.PCG64(41))
+    img = g.poisson(200.0, size=shape) + g.normal(0, 5.0, size=shape)
+    for y0 in range(7, h - side, 64):
+        for x0 in range(5, w - side, 64):
+            img[y0:y0 + side:step, x0:x0 + side:step] += g.uniform(2000, 20000, (-(-side // step),) * 2)
+    img = img.astype(F32)
+    r = oracle.lacosmic(img, 1.0, 5.0, 8.0, 1e-4, 0.01, 4, nthreads=host_threads())
+    for _ in range(5):
+        m, c, st = L.run_ex(to_dev(img), L.make_params(1.0, 5.0, 8.0, 1e-4, 0.01, 4))
+        assert_bits_equal(m.cpu().numpy(), r["mask"], "mask")
+        assert_bits_equal(c.cpu().numpy(), r["clean"], "clean")
+        assert [st.n_new[k] for k in range(4)] == list(r["n_new"])
+
+
 def test_dense_frames_in_a_batch():
     from paper_2602_17938_amd import synth
     L = lac()

@@ -851,13 +851,14 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
   // its CU, none on tiles without defects.  (6400 x 9600 uint16, 1e-3 of the
   // pixels zero: 1.11 -> 0.66 ms, the sparse passes 0.71.  Small tiles have few
   // pixels: their hits cost less than this.)
-  if (TW_ == 64 && __builtin_expect(npc > (unsigned int)ICAP && s.margin <= 0x1.fffffep127f, 0)) {  // (uniform)
+  if (TW_ == 64 && __builtin_expect(npc > (unsigned int)ICAP, 0)) {  // (uniform)
     // in the pool: a bit for each of the region's cells, the bit rows of the
     // medians below v, and the values v is taken from
     uint32_t* cells = reinterpret_cast<uint32_t*>(s.s4);
     uint32_t* low_med = cells + RH * RW / 32 + 4;
     float* levels = reinterpret_cast<float*>(low_med + RH * NW);
     static_assert(RH * RW / 32 <= NT && RH * RW / 8 + 16 + RH * NW * 4 + 64 <= (int)sizeof(s.s4), "they fit");
+    next_phase();
     float v = __int_as_float(0xff800000);
 #pragma unroll
     for (int j = 0; j < PP; ++j) {
@@ -884,8 +885,9 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       v = __shfl(v, at ? __ffsll((long long)at) - 1 : 0);
     }
     const float t = candidate_bound(sigclip, noise_from_med<false>(fkey(v), nc, f.rn2), s.margin);
-    // (where it brings little, many hits stay too many)
-    if (t > (npc > 2u * ICAP ? 1.5f : 1.1f) * thr) {  // (uniform; false for a NaN)
+    // (where it brings little, many hits stay too many; where the bound does
+    // not apply, its margin is infinite)
+    if (t > (npc > 2u * ICAP ? 1.5f : 1.1f) * s.thr) {  // (uniform; false for a NaN)
       if (tid == 0) s.cnt = 0u;
       // [C < v] of the region's cells, one after another: 32 each thread, read
       // from a different quarter row on in each lane (the banks)
@@ -1089,6 +1091,9 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       }
     }
   };
+  auto from_plane = [&](int r, int q, int* v) __attribute__((always_inline)) {
+    iter_plane_window(f, ry0 + r, rx0 + q, v);
+  };
   // By blocks near the candidates.  False (and no bit set) if the pixels to
   // evaluate exceed the list.
   auto detect = [&]() __attribute__((always_inline)) -> bool {
@@ -1111,15 +1116,16 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     // S plane, which holds nothing else meanwhile -- tiles beside this one store
     // the same values there -- and the pool's place has the list.  (A small
     // tile's pool holds every block.)
-    const bool big = QCAP < QR * QC && nq > (unsigned int)QCAP;
-    uint16_t* list = big ? reinterpret_cast<uint16_t*>(s.s4) : s.lst;
-    const unsigned int cap = big ? sizeof(s.s4) / 2 : ICAP;
+    const bool big = QCAP < QR * QC && __builtin_expect(nq > (unsigned int)QCAP, 0);
     // S at the pixels of block j's part: PX of its pixels, in each of 4 / PX
     // lanes.  Those that are live candidates of the rows, or next to one with
     // S > lo (G2 off the candidates matters within 2 pixels of the tile), are
     // listed.  (Whole waves run this.)
-    auto blocks = [&](auto px) __attribute__((always_inline)) {
+    auto blocks = [&](auto px, auto in_plane) __attribute__((always_inline)) {
       constexpr int PX = decltype(px)::value, LANES = 4 / PX;
+      constexpr bool PLANE = decltype(in_plane)::value;
+      uint16_t* list = PLANE ? reinterpret_cast<uint16_t*>(s.s4) : s.lst;
+      constexpr unsigned int cap = PLANE ? sizeof(s.s4) / 2 : ICAP;
 #pragma unroll 1
       for (unsigned int j0 = 0; j0 < nq; j0 += NT / LANES) {
         const unsigned int j = j0 + tid / LANES;
@@ -1146,7 +1152,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
             if (rb != y + a) cw[a] = 0u;
           }
           iter_block<PX>(s, f, nc, y, x, nonneg, S);
-          if (PX == 4 && big) {
+          if (PLANE) {
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
               const int r = y + (k >> 1), q = x + (k & 1);
@@ -1158,7 +1164,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
             *reinterpret_cast<float2*>(&s.s4[j][2 * part]) = float2{S[0], S[1 % PX]};
           else
             s.s4[j][part] = S[0];
-          if (part == 0 && !big) s.qmap[br * QC + bc] = (typename SM::QIndex)j;
+          if (part == 0 && !PLANE) s.qmap[br * QC + bc] = (typename SM::QIndex)j;
 #pragma unroll
           for (int k = 0; k < PX; ++k) {
             const int a = k / COLS, b = k % COLS, r = y + a, q = x + b;
@@ -1180,24 +1186,27 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
     // A block's four medians together take 308 operations, two of a row 212,
     // one alone 184: fewer blocks than lanes, less work per lane.
     if (4 * nq <= (unsigned int)NT)
-      blocks(std::integral_constant<int, 1>{});
+      blocks(std::integral_constant<int, 1>{}, std::false_type{});
     else if (2 * nq <= (unsigned int)NT)
-      blocks(std::integral_constant<int, 2>{});
+      blocks(std::integral_constant<int, 2>{}, std::false_type{});
+    else if (!big)
+      blocks(std::integral_constant<int, 4>{}, std::false_type{});
     else
-      blocks(std::integral_constant<int, 4>{});
+      blocks(std::integral_constant<int, 4>{}, std::true_type{});
     __syncthreads();
     next_phase();
     const unsigned int n2 = s.n2;
-    if (n2 > cap) {
+    if (n2 > (big ? (unsigned int)sizeof(s.s4) / 2 : (unsigned int)ICAP)) {
       __syncthreads();  // (every wave has read the count before it is cleared)
       return false;
     }
-    evaluate(list, n2, [&](int r, int q, int* v) __attribute__((always_inline)) {
-      if (big)
-        iter_plane_window(f, ry0 + r, rx0 + q, v);
-      else
-        iter_pool_window(s, f, r, q, ry0, rx0, inner, v);
-    });
+    auto pool = [&](int r, int q, int* v) __attribute__((always_inline)) {
+      iter_pool_window(s, f, r, q, ry0, rx0, inner, v);
+    };
+    if (!big)
+      evaluate(s.lst, n2, pool);
+    else
+      evaluate(reinterpret_cast<const uint16_t*>(s.s4), n2, from_plane);
     __syncthreads();
     return true;
   };
@@ -1266,8 +1275,7 @@ __device__ __forceinline__ void tile_iter(const FrameDev& f, int it, int tile, c
       for (uint32_t want = wt ? s.word(kBitD1, wr, ww) : 0u; want; want &= want - 1, ++at)
         if (at < LCAP) list[at] = (uint16_t)(wr * RW + 32 * ww + __ffs((int)want) - 1);
       __syncthreads();
-      evaluate(list, min(n2 - c0, LCAP),
-               [&](int r, int q, int* v) __attribute__((always_inline)) { iter_plane_window(f, ry0 + r, rx0 + q, v); });
+      evaluate(list, min(n2 - c0, LCAP), from_plane);
       __syncthreads();
     }
   };
